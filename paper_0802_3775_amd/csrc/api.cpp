@@ -385,14 +385,53 @@ int row_pitch(int nx) {
 // Device (padded) index of host (dense) cell o.
 size_t pitched(const fdtd_plan* p, size_t o) { return (o / (size_t)p->g.nx) * (size_t)p->px + o % (size_t)p->g.nx; }
 // Copies between a dense host array of ncell elements of elem bytes and the
-// padded device array at dev (one row of nx elements per (j, k)).
+// padded device array at dev (one row of nx elements per (j, k)).  The device
+// array moves in contiguous pieces and the padding is put in or left out on the
+// host: a 2-D copy to pageable memory goes one row at a time, 6.9 us each (one
+// component of a 200^3 grid took 274 ms).  Unpadded rows are one plain copy;
+// padded ones go through a buffer that stays in the CPU's cache.  Both return
+// with the copy done.
+constexpr size_t kRowPieceBytes = (size_t)2 << 20;
+template <class Piece>
+hipError_t row_pieces(const fdtd_plan* p, size_t elem, Piece&& piece) {
+  const size_t rows = (size_t)p->g.ny * p->g.nz, pitch = elem * (size_t)p->px;
+  const size_t per = std::max<size_t>(1, std::min(rows, kRowPieceBytes / pitch));
+  std::unique_ptr<uint8_t[]> buf(new (std::nothrow) uint8_t[per * pitch]);
+  if (!buf) return hipErrorOutOfMemory;
+  for (size_t r = 0; r < rows; r += per) {
+    const hipError_t e = piece(buf.get(), r, std::min(per, rows - r), pitch);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 hipError_t copy_rows_to_device(const fdtd_plan* p, void* dev, const void* host, size_t elem, hipStream_t st) {
   const size_t w = elem * (size_t)p->g.nx;
-  return hipMemcpy2DAsync(dev, elem * (size_t)p->px, host, w, w, (size_t)p->g.ny * p->g.nz, hipMemcpyHostToDevice, st);
+  auto copy = [&](void* to, const void* from, size_t bytes) {
+    const hipError_t e = hipMemcpyAsync(to, from, bytes, hipMemcpyHostToDevice, st);
+    return e == hipSuccess ? hipStreamSynchronize(st) : e;
+  };
+  if (p->px == p->g.nx) return copy(dev, host, w * (size_t)p->g.ny * p->g.nz);
+  return row_pieces(p, elem, [&](uint8_t* buf, size_t r0, size_t n, size_t pitch) {
+    for (size_t r = 0; r < n; ++r) {
+      std::memcpy(buf + r * pitch, (const uint8_t*)host + (r0 + r) * w, w);
+      std::memset(buf + r * pitch + w, 0, pitch - w);
+    }
+    return copy((uint8_t*)dev + r0 * pitch, buf, n * pitch);
+  });
 }
 hipError_t copy_rows_to_host(const fdtd_plan* p, void* host, const void* dev, size_t elem, hipStream_t st) {
   const size_t w = elem * (size_t)p->g.nx;
-  return hipMemcpy2DAsync(host, w, dev, elem * (size_t)p->px, w, (size_t)p->g.ny * p->g.nz, hipMemcpyDeviceToHost, st);
+  auto copy = [&](void* to, const void* from, size_t bytes) {
+    const hipError_t e = hipMemcpyAsync(to, from, bytes, hipMemcpyDeviceToHost, st);
+    return e == hipSuccess ? hipStreamSynchronize(st) : e;
+  };
+  if (p->px == p->g.nx) return copy(host, dev, w * (size_t)p->g.ny * p->g.nz);
+  return row_pieces(p, elem, [&](uint8_t* buf, size_t r0, size_t n, size_t pitch) {
+    const hipError_t e = copy(buf, (const uint8_t*)dev + r0 * pitch, n * pitch);
+    if (e != hipSuccess) return e;
+    for (size_t r = 0; r < n; ++r) std::memcpy((uint8_t*)host + (r0 + r) * w, buf + r * pitch, w);
+    return hipSuccess;
+  });
 }
 int pml_t(const fdtd_plan* p, int w) {
   return p->g.bc[w] == FDTD_BC_PEC ? p->g.pml_lo[w] + p->g.pml_hi[w] : 0;
