@@ -455,17 +455,31 @@ int gain_model_of(const std::vector<fdtd_material>& mats) {
 // matrix 18 floats in and out (144).
 
 // Bytes a step streams through: both field buffers, the material map, the psi
-// slabs and the gain arrays.  Above four times the Infinity Cache (256 MB on
-// MI355X) the field stores go out non-temporal; between one and four times it
-// part of the next step's reads still hit there (measured on a 0.46 GB grid).
+// slabs and the gain arrays (counted for every cell): what member groups are
+// sized by.
 constexpr size_t kInfinityCacheBytes = (size_t)256 << 20;
-constexpr size_t kNonTemporalBytes = 4 * kInfinityCacheBytes;
 size_t step_state_bytes(const fdtd_plan* p) {
   // (the cells a step touches: row padding is never read or written)
   size_t b = (size_t)p->ncell * 49;
   for (int w = 0; w < 3; ++w) b += 6 * 4 * psi_elems(p, w);
   if (p->has_gain) b += (size_t)p->ncell * (p->gm == 2 ? 144 : 48);
   return b;
+}
+
+// Field stores go out non-temporal when the state of a step (the gain arrays by
+// the cells that have them) exceeds the Infinity Cache: the next step finds
+// little of it there, and ordinary stores only displace what is still to be read.
+// Microseconds per step, ordinary against non-temporal, by state: Lorentz boxes
+// 195 MiB 89.3 / 99.6, 241 MiB 108.0 / 108.7, 485 MiB 156.6 / 150.5;
+// density-matrix boxes 229 MiB 158.7 / 162.6, 286 MiB 193.9 / 190.1, 457 MiB
+// 324.5 / 315.6; z-CPML slabs 255 MiB 78.6 / 73.6, 331 MiB 85.9 / 82.9; the
+// 200^3 box with CPML on all faces (440 MiB) 153.7 / 141.9.
+bool stores_nontemporal(const fdtd_plan* p) {
+  size_t b = (size_t)p->ncell * 49;
+  for (int w = 0; w < 3; ++w) b += 6 * 4 * psi_elems(p, w);
+  if (p->gm == 1) b += (size_t)p->ncell * 4 + (size_t)p->hdesc.ngain * 48;
+  if (p->gm == 2) b += (size_t)p->hdesc.ngain * 96;
+  return b > kInfinityCacheBytes;
 }
 
 // z ranges of the tiles: split at the CPML slab interfaces, then into chunks.
@@ -1374,7 +1388,7 @@ int fdtd_bind_arena(fdtd_plan* p, void* dev, size_t bytes, int64_t max_steps, vo
   p->step = 0;
   p->ntst = p->tune.stores == FDTD_STORES_NONTEMPORAL ? 1
             : p->tune.stores == FDTD_STORES_ORDINARY ? 0
-            : (step_state_bytes(p) > kNonTemporalBytes ? 1 : 0);
+            : (stores_nontemporal(p) ? 1 : 0);
   p->bound = true;
   return FDTD_OK;
 }
