@@ -68,7 +68,8 @@ struct Layout {
   size_t probe;
   size_t fluxT[FD_MAXFLUX], fluxf[FD_MAXFLUX], fluxacc[FD_MAXFLUX], fluxring[FD_MAXFLUX], fluxprev[FD_MAXFLUX];
   size_t fluxrot[FD_MAXFLUX];
-  size_t energy;
+  size_t fluxsum[FD_MAXFLUX], fluxTs[FD_MAXFLUX];  // reads: spectrum parts, T(t) samples
+  size_t energy, energys;
   size_t tiles[FD_NCLASS];
   size_t dft;
   size_t sites;
@@ -512,6 +513,8 @@ std::vector<std::pair<int, int>> z_chunks(const fdtd_plan* p, int zchunk) {
   return out;
 }
 
+size_t spectrum_parts(int plane) { return ((size_t)plane + FD_SPEC_PTS - 1) / FD_SPEC_PTS; }
+
 int compute_layout(fdtd_plan* p, int64_t max_steps, Layout& L) {
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -575,11 +578,15 @@ int compute_layout(fdtd_plan* p, int64_t max_steps, Layout& L) {
       L.fluxring[f] = dft ? take(sizeof(float) * FD_DFT_RING * 4 * (size_t)plane) : 0;
       L.fluxprev[f] = dft ? take(sizeof(double) * 2 * 4 * p->flux[f].f.size() * (size_t)plane) : 0;
       L.fluxrot[f] = dft ? take(sizeof(double) * 6 * p->flux[f].f.size()) : 0;
+      L.fluxsum[f] = dft ? take(sizeof(double) * p->flux[f].f.size() * spectrum_parts(plane)) : 0;
+      L.fluxTs[f] = take(sizeof(double) * (size_t)std::max<int64_t>(max_steps, 1));
     } else {
+      L.fluxsum[f] = L.fluxTs[f] = 0;
       L.fluxT[f] = L.fluxf[f] = L.fluxacc[f] = L.fluxring[f] = L.fluxprev[f] = L.fluxrot[f] = 0;
     }
   }
   L.energy = p->ke > 0 ? take(sizeof(double) * (size_t)(max_steps / p->ke + 1) * (size_t)p->ntiles) : 0;
+  L.energys = p->ke > 0 ? take(sizeof(double) * (size_t)(max_steps / p->ke + 1)) : 0;
   for (int c = 0; c < FD_NCLASS; ++c) L.tiles[c] = take(sizeof(fd_tile) * (size_t)p->ntiles);
   size_t ndft = 0;
   for (const Flux& f : p->flux)
@@ -1500,19 +1507,17 @@ int fdtd_read_flux(fdtd_plan* p, int32_t id, double* T, double* spec, int64_t* n
   hipStream_t st = (hipStream_t)stream;
   const double dx2 = p->dx * p->dx;
   if (T && p->step > 0) {
-    std::vector<double> part((size_t)p->step * p->nblk);
-    HIPCHK(hipMemcpyAsync(part.data(), p->arena + p->L.fluxT[id], sizeof(double) * part.size(), hipMemcpyDeviceToHost, st));
+    // the samples' partial sums are added up on the device
+    HIPCHK(fd_launch_row_sums(at<double>(p, p->L.fluxT[id]), p->step, p->nblk, at<double>(p, p->L.fluxTs[id]), st));
+    HIPCHK(hipMemcpyAsync(T, p->arena + p->L.fluxTs[id], sizeof(double) * (size_t)p->step, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    for (int64_t s = 0; s < p->step; ++s) {
-      double acc = 0.0;
-      for (int b = 0; b < p->nblk; ++b) acc += part[(size_t)s * p->nblk + b];
-      T[s] = acc * dx2;
-    }
+    for (int64_t s = 0; s < p->step; ++s) T[s] *= dx2;
   }
   const Flux& fl = p->flux[id];
   if (spec && fl.nf > 0) {
-    const size_t plane = (size_t)p->px * p->g.ny;  // padded points (their sums stay 0)
-    std::vector<double> acc(2 * 4 * (size_t)fl.nf * plane);
+    const int plane = p->px * p->g.ny;  // padded points (their sums stay 0)
+    const size_t nb = spectrum_parts(plane);
+    std::vector<double> parts((size_t)fl.nf * nb);
     // samples taken at steps 0, decim, ... < step; complete rings are already in
     // the sums, the rest is added into a copy
     const int64_t nsamp = (p->step + fl.decim - 1) / fl.decim;
@@ -1522,17 +1527,13 @@ int fdtd_read_flux(fdtd_plan* p, int32_t id, double* T, double* spec, int64_t* n
       HIPCHK(fd_launch_dft_preview(p->ddft, (int)p->dft.size(), id, nsamp - pending, pending, st));
       src = p->L.fluxprev[id];
     }
-    HIPCHK(hipMemcpyAsync(acc.data(), p->arena + src, sizeof(double) * acc.size(), hipMemcpyDeviceToHost, st));
+    HIPCHK(fd_launch_spectrum(at<double>(p, src), fl.nf, plane, at<double>(p, p->L.fluxsum[id]), st));
+    HIPCHK(hipMemcpyAsync(parts.data(), p->arena + p->L.fluxsum[id], sizeof(double) * parts.size(),
+                          hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     for (int q = 0; q < fl.nf; ++q) {
       double sum = 0.0;
-      for (size_t pt = 0; pt < plane; ++pt) {
-        const double* ex = &acc[2 * ((0 * (size_t)fl.nf + q) * plane + pt)];
-        const double* ey = &acc[2 * ((1 * (size_t)fl.nf + q) * plane + pt)];
-        const double* hx = &acc[2 * ((2 * (size_t)fl.nf + q) * plane + pt)];
-        const double* hy = &acc[2 * ((3 * (size_t)fl.nf + q) * plane + pt)];
-        sum += (ex[0] * hy[0] + ex[1] * hy[1]) - (ey[0] * hx[0] + ey[1] * hx[1]);
-      }
+      for (size_t b = 0; b < nb; ++b) sum += parts[(size_t)q * nb + b];
       spec[q] = sum * dx2;
     }
   }
@@ -1622,15 +1623,11 @@ int fdtd_read_energy(fdtd_plan* p, double* host, int64_t* n, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   const int64_t ns = (p->step + p->ke - 1) / p->ke;
   if (ns > 0) {
-    std::vector<double> part((size_t)ns * p->ntiles);
-    HIPCHK(hipMemcpyAsync(part.data(), p->arena + p->L.energy, sizeof(double) * part.size(), hipMemcpyDeviceToHost, st));
+    HIPCHK(fd_launch_row_sums(at<double>(p, p->L.energy), ns, p->ntiles, at<double>(p, p->L.energys), st));
+    HIPCHK(hipMemcpyAsync(host, p->arena + p->L.energys, sizeof(double) * (size_t)ns, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     const double w = 0.5 * p->dx * p->dx * p->dx;
-    for (int64_t s = 0; s < ns; ++s) {
-      double acc = 0.0;
-      for (int t = 0; t < p->ntiles; ++t) acc += part[(size_t)s * p->ntiles + t];
-      host[s] = acc * w;
-    }
+    for (int64_t s = 0; s < ns; ++s) host[s] *= w;
   }
   *n = ns;
   return FDTD_OK;

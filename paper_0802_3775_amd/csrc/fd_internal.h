@@ -176,6 +176,12 @@ hipError_t fd_launch_dft(const fd_dft_tile* tiles, int ntiles, int s, hipStream_
                          hipEvent_t stop = nullptr);
 hipError_t fd_launch_dft_preview(const fd_dft_tile* tiles, int ntiles, int flux, long long first, int count,
                                  hipStream_t st);
+// Sums for reads.  Spectrum: parts[q * nb + b] = sum of Re(Ex Hy* - Ey Hx*) over
+// the FD_SPEC_PTS plane points of part b (nb = parts of the plane) of the complex
+// sums acc [4][nf][plane][2].  Rows: out[r] = sum of part[r * m ...] in order.
+#define FD_SPEC_PTS 4096
+hipError_t fd_launch_spectrum(const double* acc, int nf, int plane, double* parts, hipStream_t st);
+hipError_t fd_launch_row_sums(const double* part, long long n, int m, double* out, hipStream_t st);
 hipError_t fd_launch_advance(fd_desc* const* descs, int n, long long k, hipStream_t st);
 hipError_t fd_launch_advance_one(fd_desc* d, long long k, hipStream_t st);
 hipError_t fd_launch_fill(void* p, size_t bytes, hipStream_t st);
