@@ -70,7 +70,7 @@ struct Layout {
   size_t fluxrot[FD_MAXFLUX];
   size_t fluxsum[FD_MAXFLUX], fluxTs[FD_MAXFLUX];  // reads: spectrum parts, T(t) samples
   size_t energy, energys;
-  size_t tiles[FD_NCLASS];
+  size_t tiles[FD_NCLASS], own[FD_NCLASS];
   size_t dft;
   size_t sites;
   size_t glist, elist, dmq[2], dmunits;  // density-matrix plans: gain-cell list, Q buffers, pass work units
@@ -129,6 +129,16 @@ fd_xcd xcd_partition(const std::vector<double>& cost, int* grid) {
   return r;
 }
 
+// Tiles by class, their algorithmic bytes (XCD balancing), the XCD partitions and
+// the device copy.
+struct TileSet {
+  std::vector<fd_tile> tiles[FD_NCLASS];
+  std::vector<double> cost[FD_NCLASS];
+  fd_xcd part[FD_NCLASS] = {};
+  int pgrid[FD_NCLASS] = {};
+  fd_tile* dev[FD_NCLASS] = {};
+};
+
 }  // namespace
 
 struct fdtd_plan {
@@ -163,12 +173,9 @@ struct fdtd_plan {
   fd_desc* ddesc = nullptr;
   int64_t step = 0;
   int nblk = 0, ntiles = 0;
-  std::vector<fd_tile> tiles[FD_NCLASS];
-  std::vector<double> tcost[FD_NCLASS];  // algorithmic bytes of each tile (XCD balancing)
-  fd_xcd part[FD_NCLASS] = {};
-  int pgrid[FD_NCLASS] = {};
-  int ntst = 0;  // non-temporal field stores: state well beyond the Infinity Cache
-  fd_tile* dtiles[FD_NCLASS] = {};
+  TileSet ts;   // the tuning's tiles: what a batch steps
+  TileSet own;  // what the plan steps alone (own_zchunk)
+  int ntst = 0;  // non-temporal field stores: state beyond the Infinity Cache
   std::vector<fd_dft_tile> dft;
   fd_dft_tile* ddft = nullptr;
   int maxnf = 0;
@@ -513,6 +520,25 @@ std::vector<std::pair<int, int>> z_chunks(const fdtd_plan* p, int zchunk) {
   return out;
 }
 
+// z-chunk of a plan stepped alone.  A step is one launch whose time is a tile's
+// set-up plus its planes, one after the other, as long as the chip has room for
+// all tiles at once; a small grid's tiles leave most of it idle, so they are cut
+// shorter until there are about three for each of the 256 CUs (or one plane each).
+// Beyond that a tile's set-up planes cost more than the shorter chains save.
+// Microseconds per step by tiles (chunk): 16^3 cell 8 (4) 6.69, 32 (1) 4.32;
+// 32^3 cell 32 (4) 6.45, 128 (1) 4.19; 39x26x102 slab 208 (4) 8.39, 412 (2) 7.21,
+// 816 (1) 7.26; 64x64x120 slab 272 (8) 12.37, 448 (5) 10.40, 720 (3) 10.47,
+// 1,150 (2) 11.36; 80x80x224 slab 930 (8) 18.9, 1,500 (5) 20.5.  A bound on the
+// workgroups keeps the tuning's tiles.
+int own_zchunk(const fdtd_plan* p) {
+  constexpr size_t kTilesAlone = 768;
+  const int zc = std::max(1, p->tune.zchunk);
+  if (p->tune.max_blocks > 0 || (size_t)p->nblk * ((p->g.nz + zc - 1) / zc) >= kTilesAlone) return zc;
+  for (int z = 1; z < zc && z < p->g.nz; ++z)
+    if ((size_t)p->nblk * z_chunks(p, z).size() <= kTilesAlone) return z;
+  return zc;
+}
+
 size_t spectrum_parts(int plane) { return ((size_t)plane + FD_SPEC_PTS - 1) / FD_SPEC_PTS; }
 
 int compute_layout(fdtd_plan* p, int64_t max_steps, Layout& L) {
@@ -588,6 +614,9 @@ int compute_layout(fdtd_plan* p, int64_t max_steps, Layout& L) {
   L.energy = p->ke > 0 ? take(sizeof(double) * (size_t)(max_steps / p->ke + 1) * (size_t)p->ntiles) : 0;
   L.energys = p->ke > 0 ? take(sizeof(double) * (size_t)(max_steps / p->ke + 1)) : 0;
   for (int c = 0; c < FD_NCLASS; ++c) L.tiles[c] = take(sizeof(fd_tile) * (size_t)p->ntiles);
+  const int zo = own_zchunk(p);
+  const size_t nown = zo < p->tune.zchunk ? (size_t)p->ntiles + (size_t)p->nblk * z_chunks(p, zo).size() : 0;
+  for (int c = 0; c < FD_NCLASS; ++c) L.own[c] = nown ? take(sizeof(fd_tile) * nown) : 0;
   size_t ndft = 0;
   for (const Flux& f : p->flux)
     if (f.nf > 0) ndft += (size_t)((plane + FD_DFT_PTS - 1) / FD_DFT_PTS) * (size_t)((f.nf + FD_DFT_QB - 1) / FD_DFT_QB);
@@ -761,9 +790,9 @@ int64_t plan_phase_key(const fdtd_plan* p, int64_t n0) {
 
 int plan_enqueue(fdtd_plan* p, int64_t n, hipStream_t st, Fork* fk) {
   int nt[FD_NCLASS];
-  for (int c = 0; c < FD_NCLASS; ++c) nt[c] = (int)p->tiles[c].size();
+  for (int c = 0; c < FD_NCLASS; ++c) nt[c] = (int)p->own.tiles[c].size();
   for (int64_t s = 0; s < n; ++s) {
-    const int r = enqueue_step(p->dtiles, nt, p->part, p->pgrid, p->tune.tile_x, p->tune.block,
+    const int r = enqueue_step(p->own.dev, nt, p->own.part, p->own.pgrid, p->tune.tile_x, p->tune.block,
                                p->tune.max_blocks, p->ddft, (int)p->dft.size(), p->maxnf,
                                plan_dft_due(p, p->step + s), (int)s, p->ntst, plan_dm(p), st, fk);
     if (r) return r;
@@ -1288,15 +1317,11 @@ int fdtd_bind_arena(fdtd_plan* p, void* dev, size_t bytes, int64_t max_steps, vo
     const int hi = std::max(0, b - std::max(a, n - d.pml_hi[w]));
     return lo + hi;
   };
-  for (int c = 0; c < FD_NCLASS; ++c) {
-    p->tiles[c].clear();
-    p->tcost[c].clear();
-  }
   std::vector<fd_tile> all;
   std::vector<double> tcost;
   std::vector<std::pair<int, int>> tcls;
   int tidx = 0;
-  for (const auto& ch : chunks) {
+  auto add_chunk = [&](std::pair<int, int> ch, int flags, int* slot) {
     for (int by = 0; by < nty; ++by)
       for (int bx = 0; bx < ntx; ++bx) {
         fd_tile t{};
@@ -1305,7 +1330,8 @@ int fdtd_bind_arena(fdtd_plan* p, void* dev, size_t bytes, int64_t max_steps, vo
         t.j0 = by * TY;
         t.k0 = ch.first;
         t.k1 = ch.second;
-        t.tidx = tidx++;
+        t.tidx = slot ? (*slot)++ : 0;
+        t.flags = flags;
         t.blk = by * ntx + bx;
         // sources, probes and flux planes the tile's kernel must look at
         for (int q = 0; q < d.nsrc; ++q) {
@@ -1345,34 +1371,62 @@ int fdtd_bind_arena(fdtd_plan* p, void* dev, size_t bytes, int64_t max_steps, vo
                                   (double)nxt_ * slab_count(1, t.j0, jend) * nzt_ +
                                   (double)nxt_ * nyt_ * slab_count(2, t.k0, t.k1);
         // algorithmic bytes of the tile, plus the plane below it that it also stages
-        tcost.push_back(49.0 * nxt_ * nyt_ * (nzt_ + 1) + 32.0 * slab_cells + (gain ? 84.0 * (double)ngain : 0.0));
+        tcost.push_back(flags & FD_TILE_ENERGY ? 0.0  // idle in most steps
+                                               : 49.0 * nxt_ * nyt_ * (nzt_ + 1) + 32.0 * slab_cells +
+                                                     (gain ? 84.0 * (double)ngain : 0.0));
         tcls.push_back({pml, gain ? 1 : 0});
         all.push_back(t);
       }
-  }
+  };
   // fold classes into fewer launches: a more general kernel is correct on a
   // simpler tile (slab and gain tests are per cell / per plane at run time)
-  int max_pml = 0, any_gain = 0;
-  for (const auto& pc : tcls) {
-    max_pml = std::max(max_pml, pc.first);
-    any_gain |= pc.second;
-  }
-  for (size_t q = 0; q < all.size(); ++q) {
-    int pml = tcls[q].first, gain = tcls[q].second;
-    if (p->tune.merge >= 1 && pml == 0 && d.pml_t[2]) pml = 1;
-    if (p->tune.merge >= 2) {
-      pml = max_pml;
-      gain = any_gain;
+  auto fold = [&](TileSet& ts, const size_t off[FD_NCLASS]) -> hipError_t {
+    int max_pml = 0, any_gain = 0;
+    for (const auto& pc : tcls) {
+      max_pml = std::max(max_pml, pc.first);
+      any_gain |= pc.second;
     }
-    p->tiles[pml + 3 * gain].push_back(all[q]);
-    p->tcost[pml + 3 * gain].push_back(tcost[q]);
-  }
-  for (int c = 0; c < FD_NCLASS; ++c) p->part[c] = xcd_partition(p->tcost[c], &p->pgrid[c]);
-  for (int c = 0; c < FD_NCLASS; ++c) {
-    p->dtiles[c] = at<fd_tile>(p, L.tiles[c]);
-    if (!p->tiles[c].empty())
-      HIPCHK(hipMemcpyAsync(p->dtiles[c], p->tiles[c].data(), sizeof(fd_tile) * p->tiles[c].size(),
-                            hipMemcpyHostToDevice, st));
+    ts = TileSet();
+    for (size_t q = 0; q < all.size(); ++q) {
+      int pml = tcls[q].first, gain = tcls[q].second;
+      if (p->tune.merge >= 1 && pml == 0 && d.pml_t[2]) pml = 1;
+      if (p->tune.merge >= 2) {
+        pml = max_pml;
+        gain = any_gain;
+      }
+      ts.tiles[pml + 3 * gain].push_back(all[q]);
+      ts.cost[pml + 3 * gain].push_back(tcost[q]);
+    }
+    for (int c = 0; c < FD_NCLASS; ++c) {
+      ts.part[c] = xcd_partition(ts.cost[c], &ts.pgrid[c]);
+      ts.dev[c] = at<fd_tile>(p, off[c]);
+      if (ts.tiles[c].empty()) continue;
+      const hipError_t e = hipMemcpyAsync(ts.dev[c], ts.tiles[c].data(), sizeof(fd_tile) * ts.tiles[c].size(),
+                                          hipMemcpyHostToDevice, st);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  };
+  for (const auto& ch : chunks) add_chunk(ch, 0, &tidx);
+  HIPCHK(fold(p->ts, L.tiles));
+  const int zo = own_zchunk(p);
+  if (zo < p->tune.zchunk) {
+    // shorter tiles, each after the tuning's tiles of its z range (which run
+    // instead of them in the steps that record the energy)
+    const auto fine = z_chunks(p, zo);
+    all.clear();
+    tcost.clear();
+    tcls.clear();
+    tidx = 0;
+    size_t f = 0;
+    for (const auto& ch : chunks) {
+      if (p->ke > 0) add_chunk(ch, FD_TILE_ENERGY, &tidx);
+      for (; f < fine.size() && fine[f].first < ch.second; ++f)
+        add_chunk(fine[f], p->ke > 0 ? FD_TILE_NOENERGY : 0, nullptr);
+    }
+    HIPCHK(fold(p->own, L.own));
+  } else {
+    p->own = p->ts;
   }
   p->dft.clear();
   for (int f = 0; f < d.nflux; ++f) {
@@ -1664,8 +1718,8 @@ int fdtd_class_cells(const fdtd_plan* p, int64_t* cells) {
   const int TX = p->tune.tile_x, TY = p->tune.block / p->tune.tile_x;
   for (int c = 0; c < FD_NCLASS; ++c) {
     int64_t acc = 0;
-    for (const fd_tile& t : p->tiles[c])
-      acc += (int64_t)std::min(TX, p->g.nx - t.i0) * std::min(TY, p->g.ny - t.j0) * (t.k1 - t.k0);
+    for (const fd_tile& t : p->own.tiles[c])
+      if (!(t.flags & FD_TILE_ENERGY)) acc += (int64_t)std::min(TX, p->g.nx - t.i0) * std::min(TY, p->g.ny - t.j0) * (t.k1 - t.k0);
     cells[c] = acc;
   }
   int64_t pts = 0;
@@ -1687,8 +1741,8 @@ int fdtd_class_bytes(const fdtd_plan* p, double* bytes) {
   };
   for (int c = 0; c < FD_NCLASS; ++c) {
     double acc = 0.0;
-    for (const fd_tile& t : p->tiles[c])
-      for (int k = t.k0; k < t.k1; ++k)
+    for (const fd_tile& t : p->own.tiles[c])
+      for (int k = t.flags & FD_TILE_ENERGY ? t.k1 : t.k0; k < t.k1; ++k)
         for (int j = t.j0; j < std::min(ny, t.j0 + TY); ++j)
           for (int i = t.i0; i < std::min(nx, t.i0 + TX); ++i) {
             double b = 49.0;
@@ -1737,12 +1791,12 @@ int fdtd_time_kernels(fdtd_plan* p, int64_t n, void* stream, double* ms, int64_t
   };
   for (int64_t s = 0; s < n; ++s) {
     for (int c = 0; c < FD_NCLASS; ++c) {
-      const int nt = (int)p->tiles[c].size();
+      const int nt = (int)p->own.tiles[c].size();
       if (nt == 0) continue;
-      const int grid = p->tune.max_blocks > 0 ? std::min(nt, p->tune.max_blocks) : p->pgrid[c];
-      const fd_xcd* pc = p->tune.max_blocks > 0 ? nullptr : &p->part[c];
+      const int grid = p->tune.max_blocks > 0 ? std::min(nt, p->tune.max_blocks) : p->own.pgrid[c];
+      const fd_xcd* pc = p->tune.max_blocks > 0 ? nullptr : &p->own.part[c];
       const int r = record(c, [&](hipEvent_t a, hipEvent_t b) {
-        return fd_launch_step(c, p->dtiles[c], nt, p->tune.tile_x, p->tune.block, grid, (int)s, pc, p->ntst, st, a,
+        return fd_launch_step(c, p->own.dev[c], nt, p->tune.tile_x, p->tune.block, grid, (int)s, pc, p->ntst, st, a,
                               b);
       });
       if (r) { cleanup(); return r; }
@@ -1948,8 +2002,8 @@ void batch_layout(fdtd_batch* b, fdtd_plan* const* plans, int32_t n, int gm) {
     g.maxnf = std::max(g.maxnf, p->maxnf);
     held += bytes;
     for (int c = 0; c < FD_NCLASS; ++c) {
-      b->tiles[c].insert(b->tiles[c].end(), p->tiles[c].begin(), p->tiles[c].end());
-      gcost[c].insert(gcost[c].end(), p->tcost[c].begin(), p->tcost[c].end());
+      b->tiles[c].insert(b->tiles[c].end(), p->ts.tiles[c].begin(), p->ts.tiles[c].end());
+      gcost[c].insert(gcost[c].end(), p->ts.cost[c].begin(), p->ts.cost[c].end());
     }
     b->dft.insert(b->dft.end(), p->dft.begin(), p->dft.end());
     b->maxnf = std::max(b->maxnf, p->maxnf);

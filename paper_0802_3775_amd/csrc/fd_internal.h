@@ -125,6 +125,12 @@ struct fd_tile {
   int flags;  // FD_TILE_ZSLAB: some plane of [k0, k1) lies in a z CPML slab
 };
 #define FD_TILE_ZSLAB 1
+// A plan stepped alone in shorter tiles than its tuning's lists both: the tuning's
+// tiles run in the steps that record the energy (whose partial sums are per tile
+// of the tuning, so that a sample is the same bit for bit in a batch and alone),
+// the shorter ones in all others.
+#define FD_TILE_ENERGY 2
+#define FD_TILE_NOENERGY 4
 
 // DFT work unit: FD_DFT_PTS plane points x 4 components x FD_DFT_QB frequencies.
 struct fd_dft_tile {

@@ -1132,6 +1132,13 @@ __device__ __forceinline__ void step_body(const fd_tile* __restrict__ tiles, int
     const int x = (int)blockIdx.x % 8, q = (int)blockIdx.x / 8;
     if (q < part.count[x]) {
       const fd_tile tl = tiles[part.start[x] + q];
+      // a plan's two tile sets take turns by whether the step records the energy
+      // (never in the looped form; steps stay below 2^31: 32-bit remainders)
+      if (tl.flags & (FD_TILE_ENERGY | FD_TILE_NOENERGY)) {
+        const cdesc* d = (const cdesc*)tl.d;
+        const bool due = (uint32_t)(d->step + s) % (uint32_t)d->ke == 0;
+        if (tl.flags & (due ? FD_TILE_NOENERGY : FD_TILE_ENERGY)) return;
+      }
       run(tl);
     }
     return;
