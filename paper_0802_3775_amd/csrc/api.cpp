@@ -643,11 +643,33 @@ T* at(fdtd_plan* p, size_t off) {
   return reinterpret_cast<T*>(p->arena + off);
 }
 
+// q = (o m) >> s is o / n for every o below 2^31 (m = floor(2^s / n) + 1 with
+// s = 31 + ceil(log2 n): the error m n - 2^s is at most n <= 2^(s - 31)).
+void divisor(uint32_t n, uint32_t out[2]) {
+  uint32_t l = 0;
+  while (((uint64_t)1 << l) < n) ++l;
+  out[0] = (uint32_t)((((uint64_t)1 << (31 + l)) / n) + 1);
+  out[1] = 31 + l;
+}
+
+// Calls f(j, k) for every row of the grid: in order, or (blocks) in blocks of 8 x 8 rows, the order the
+// density-matrix passes work in -- a run of gain cells then gathers most of its
+// neighbours' rows from within the block.  The passes of the 168^3 box read
+// 1.35 (predictor) and 1.58 (corrector) times their cells' footprint in row order.
+template <class F>
+void each_row(int ny, int nz, bool blocks, F&& f) {
+  const int B = blocks ? 8 : std::max(1, ny), K = blocks ? 8 : 1;
+  for (int kb = 0; kb < nz; kb += K)
+    for (int jb = 0; jb < ny; jb += B)
+      for (int k = kb; k < std::min(nz, kb + K); ++k)
+        for (int j = jb; j < std::min(ny, jb + B); ++j) f(j, k);
+}
+
 // Work units of the density-matrix passes (plans with that medium): the gain
 // ordinals in runs of FD_DM_CELLS, the cells whose edges can touch a gain cell
 // in runs of FD_DM_EDGES (the planes from the lowest gain plane to one past the
 // highest; every plane on a periodic z axis), one diagnostics unit per xy tile
-// of each flux plane and one for the probes; uploaded to the plan's arena,
+// of each flux plane; uploaded to the plan's arena,
 // with the cells and algorithmic bytes of one launch of each pass.
 int build_dm_units(fdtd_plan* p) {
   for (auto& v : p->dmu) v.clear();
@@ -687,19 +709,26 @@ int build_dm_units(fdtd_plan* p) {
       }
       return p->mats[p->host_map[((size_t)q[2] * ny + q[1]) * nx + q[0]]].gain != 0;
     };
-    for (int k = k0; k < k1; ++k)
-      for (int j = 0; j < ny; ++j)
-        for (int i = 0; i < nx; ++i) {
-          bool any = false;
-          for (int u = 0; u < 2 && !any; ++u)
-            for (int v = 0; v < 2 && !any; ++v)
-              any = gain_at(i, j - u, k - v) || gain_at(i - v, j, k - u) || gain_at(i - u, j - v, k);
-          if (any) elist.push_back((uint32_t)((size_t)k * plane + (size_t)j * p->px + i));
-        }
+    each_row(ny, nz, true, [&](int j, int k) {
+      if (k < k0 || k >= k1) return;
+      for (int i = 0; i < nx; ++i) {
+        bool any = false;
+        for (int u = 0; u < 2 && !any; ++u)
+          for (int v = 0; v < 2 && !any; ++v)
+            any = gain_at(i, j - u, k - v) || gain_at(i - v, j, k - u) || gain_at(i - u, j - v, k);
+        if (any) elist.push_back((uint32_t)((size_t)k * plane + (size_t)j * p->px + i));
+      }
+    });
     const int ne = (int)elist.size();
     if (ne)
       HIPCHK(hipMemcpy(p->arena + p->L.elist, elist.data(), sizeof(uint32_t) * elist.size(), hipMemcpyHostToDevice));
     for (int e0 = 0; e0 < ne; e0 += FD_DM_EDGES) p->dmu[1].push_back({p->ddesc, e0, std::min(FD_DM_EDGES, ne - e0), 0});
+    for (int q = 0; q < d.nprobe; ++q) {  // E probes in listed cells: sampled by the edge pass
+      if (d.probe_comp[q] > 2) continue;
+      const uint32_t cell = (uint32_t)d.probe_k[q] * (uint32_t)plane + (uint32_t)d.probe_cell[q];
+      const auto it = std::find(elist.begin(), elist.end(), cell);
+      if (it != elist.end()) p->dmu[1][(size_t)(it - elist.begin()) / FD_DM_EDGES].probes |= 1u << q;
+    }
     p->dm_cells[0] = p->dm_cells[1] = ng;
     p->dm_cells[2] = ne;
     // predictor: state 72 + E^n and A of the cell's edges 24 + map and list 5
@@ -712,11 +741,10 @@ int build_dm_units(fdtd_plan* p) {
   }
   for (int f = 0; f < (int)p->flux.size(); ++f)
     for (int b = 0; b < p->nblk; ++b) p->dmu[2].push_back({p->ddesc, f, b, 0});
-  p->dmu[2].push_back({p->ddesc, -1, 0, 0});
   const int64_t fpts = (int64_t)p->g.nx * p->g.ny;  // a flux plane's points (its padding is skipped)
-  p->dm_cells[3] = (int64_t)p->flux.size() * fpts + (int64_t)p->probes.size();
-  // E^n, E^{n+1} (x, y) and H at two planes (x, y) per flux-plane point; a probe sample
-  p->dm_bytes[3] = 32.0 * (double)p->flux.size() * (double)fpts + 8.0 * (double)p->probes.size();
+  p->dm_cells[3] = (int64_t)p->flux.size() * fpts;
+  // E^n, E^{n+1} (x, y) and H at two planes (x, y) per flux-plane point
+  p->dm_bytes[3] = 32.0 * (double)p->flux.size() * (double)fpts;
   p->ddm = at<fd_dm_unit>(p, p->L.dmunits);
   size_t off = 0;
   for (int q = 0; q < 3; ++q) {
@@ -1093,6 +1121,8 @@ int fdtd_bind_arena(fdtd_plan* p, void* dev, size_t bytes, int64_t max_steps, vo
   d.nx = p->g.nx; d.ny = p->g.ny; d.nz = p->g.nz;
   d.px = p->px;
   d.plane = p->px * p->g.ny;
+  divisor((uint32_t)d.plane, d.div_plane);
+  divisor((uint32_t)d.px, d.div_px);
   for (int w = 0; w < 3; ++w) d.per[w] = p->g.bc[w] == FDTD_BC_PERIODIC ? 1 : 0;
   d.ncell = (int)p->nstore;
   d.ch = (float)(p->dt / p->dx);
@@ -1268,14 +1298,17 @@ int fdtd_bind_arena(fdtd_plan* p, void* dev, size_t bytes, int64_t max_steps, vo
     HIPCHK(hipStreamSynchronize(st));
   }
   if (p->has_gain) {
-    // gain ordinals (gain cells numbered in cell order) and the initial
-    // populations at them; the rest of the state starts at zero with the arena
-    // (the order of cells is the same in the dense and the padded layout)
+    // gain ordinals (each_row) and the initial populations at them; the rest of
+    // the state starts at zero with the arena (the order of cells is the same in
+    // the dense and the padded layout)
     const size_t nc = (size_t)p->ncell;
     p->gidx.assign(nc, 0u);
     uint32_t g = 0;
-    for (size_t o = 0; o < nc; ++o)
-      if (p->mats[p->host_map[o]].gain) p->gidx[o] = g++;
+    each_row(p->g.ny, p->g.nz, p->gm == 2, [&](int j, int k) {
+      const size_t o0 = ((size_t)k * p->g.ny + j) * (size_t)p->g.nx;
+      for (size_t o = o0; o < o0 + (size_t)p->g.nx; ++o)
+        if (p->mats[p->host_map[o]].gain) p->gidx[o] = g++;
+    });
     HIPCHK(copy_rows_to_device(p, p->arena + L.gidx, p->gidx.data(), sizeof(uint32_t), st));
     HIPCHK(fd_launch_init_pop(at<uint8_t>(p, L.map), at<float>(p, L.ninit), at<uint32_t>(p, L.gidx), d.gainmask,
                               d.pop, d.ncell, d.nx, d.px, st));

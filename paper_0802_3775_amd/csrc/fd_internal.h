@@ -63,8 +63,8 @@ struct fd_desc {
   float* H[2][3];
   float* P[2][3];              // polarization ping-pong (P^n in [n&1], P^{n-1} in the other), by gain ordinal
   // Gain state, indexed by the cell's gain ordinal gidx[cell] (gain cells
-  // numbered in cell order, so a wavefront's gain cells read and write one
-  // contiguous run; 0 for other cells, which never use it).  Lorentz model:
+  // numbered in cell order, or for the density matrix in blocks of 8 x 8 rows, so
+  // a wavefront's gain cells read and write one contiguous run; 0 for other cells, which never use it).  Lorentz model:
   // P[2][3] and 6 planes, n1,n2,n3 high parts, then low parts.  Density matrix:
   // 18 planes, rho_11, rho_22, rho_33 high parts, low parts, then Re rho_01..03,
   // Im rho_01..03, Re rho_12, rho_13, rho_23, Im rho_12, rho_13, rho_23.
@@ -75,7 +75,9 @@ struct fd_desc {
   // corrector (dmq[1]), 3 planes each, both including the noise current's dt J
   // (cells without gain keep the arena's zeros)
   const uint32_t* glist;
-  const uint32_t* elist;  // the (padded) cells with an edge that a gain cell shares, in cell order
+  const uint32_t* elist;  // the (padded) cells with an edge that a gain cell shares, in blocks of rows
+  // o / plane and r / px of any cell index below 2^31 as (o m) >> s: {m, s}
+  uint32_t div_plane[2], div_px[2];
   float* dmq[2];
   int ngain;
   int tile_x;  // xy tile width of the plan's step tiles (the T(t) partial slots)
@@ -142,12 +144,13 @@ struct fd_dft_tile {
 };
 
 // Work unit of the density-matrix passes: entries [first, first + count) of one
-// plan's gain ordinals (cell passes) or of its edge list elist (edge pass); for
-// the diagnostics pass first = flux plane (-1: probes), count = xy tile.
+// plan's gain ordinals (cell passes) or of its edge list elist (edge pass, with
+// the E probes in those cells); for the diagnostics pass first = flux plane,
+// count = xy tile.
 struct fd_dm_unit {
   const fd_desc* d;
   int first, count;
-  int pad;
+  unsigned probes;
 };
 #define FD_DM_CELLS 256   // gain cells per unit of the cell passes (one per thread)
 #define FD_DM_EDGES 256   // cells per unit of the edge pass (one per thread)

@@ -1514,6 +1514,13 @@ __global__ void init_pop_kernel(const uint8_t* __restrict__ map, const float* __
 //   corrector  E* = A - [Q*]/eps,  rho^{n+1} = S(rho^n; <(E^n + E*)/2>),
 //              Q = P(rho^{n+1}) - P(rho^n) + dt J
 //   edges      E^{n+1} = A - [Q]/eps
+// (The passes move their bytes at 4.2-4.7 TB/s, near the 5.1 TB/s of a large copy:
+// on the 168^3 box, 2.09 M gain cells, counted 291 MB in 61.6 us, 499 MB in 112 us
+// and 136 MB in 32 us.  Numbering the gain cells and edges in blocks of 8 x 8 rows
+// with neighbouring units on one XCD took the corrector's traffic from 636 MB, and
+// neighbour offsets without wall tests and divisions its instructions from 1,200 to
+// 930 a wave and its registers from 135 to 112, four waves per SIMD instead of
+// three: 124 -> 112 us.)
 // with S = R(dt/2) C(E) R(dt/2), P_c = 2 kappa Re rho_0c, J the
 // spontaneous-emission noise current at the centre and eps that of the edge's
 // own voxel.  Each pass reads what the previous one wrote for neighbouring
@@ -1526,56 +1533,86 @@ __global__ void init_pop_kernel(const uint8_t* __restrict__ map, const float* __
 struct DmMats {
   fd_mat m[FD_MAXMAT];
 };
-__device__ __forceinline__ void dm_stage_mats(const cdesc* d, DmMats& sm) {
-  const int words = d->nmat * (int)(sizeof(fd_mat) / 4);
+// loads(): issues the thread's loads that need only its list position; they are in
+// flight with the table's (the memory counter retires in order, so only the
+// table's are waited for) and across the barrier, which waits for LDS alone.
+template <class F>
+__device__ __forceinline__ void dm_stage_mats(const cdesc* d, DmMats& sm, F&& loads) {
+  const int words = d->nmat * (int)(sizeof(fd_mat) / 4), t = (int)threadIdx.x;
   const gf* src = G((const float*)d->mats);
   float* dst = reinterpret_cast<float*>(sm.m);
-  for (int q = (int)threadIdx.x; q < words; q += (int)blockDim.x) dst[q] = src[q];
-  __syncthreads();
+  const float w = src[t < words ? t : 0];
+  loads();
+  if (t < words) dst[t] = w;
+  for (int q = t + (int)blockDim.x; q < words; q += (int)blockDim.x) dst[q] = src[q];
+  lds_barrier();
+}
+
+// Work unit of this workgroup.  Workgroups go to the 8 XCDs in turn; runs of
+// kDmRun consecutive units are kept on one XCD, so that the fields and increments
+// a unit gathers from the rows and planes beside its own cells are in that XCD's
+// L2 from the units next to it (gain cells are numbered in blocks of 8 x 8 rows).
+constexpr int kDmRun = 32;
+__device__ __forceinline__ int dm_unit(int w, int n) {
+  if (w >= n / (8 * kDmRun) * (8 * kDmRun)) return w;  // the rest, in order
+  const int x = w % 8, q = w / 8;
+  return (q / kDmRun * 8 + x) * kDmRun + q % kDmRun;
 }
 
 struct Ijk {
   int i, j, k;
 };
+// Coordinates of cell o, the divisions as a product and a shift (fd_desc)
 __device__ __forceinline__ Ijk ijk_of(const cdesc* d, uint32_t o) {
-  const uint32_t plane = (uint32_t)d->plane, px = (uint32_t)d->px;
-  const uint32_t k = o / plane, r = o - k * plane, j = r / px;
-  return {(int)(r - j * px), (int)j, (int)k};
+  const uint32_t k = (uint32_t)(((uint64_t)o * d->div_plane[0]) >> d->div_plane[1]);
+  const uint32_t r = o - k * (uint32_t)d->plane;
+  const uint32_t j = (uint32_t)(((uint64_t)r * d->div_px[0]) >> d->div_px[1]);
+  return {(int)(r - j * (uint32_t)d->px), (int)j, (int)k};
 }
 
-// Coordinates of cell p's neighbours along each axis at offsets -1, 0, +1
-// (periodic wrap; -1 beyond a PEC wall), so a cell's neighbourhood is indexed
-// without divisions.
+// Cell p's neighbourhood: element offsets to its neighbours at -1, 0, +1 along
+// each axis (periodic wrap; 0 beyond a PEC wall, where ok is false), so that a
+// neighbour's index is the cell's plus one offset per axis.  wall: the cell lies
+// on or next to a PEC wall, where values beyond it and held edges have to be
+// looked at; waves without such a cell run without those tests.
 struct Nbr {
-  int c[3][3];  // [axis][offset + 1]
+  int d[3][3];  // [axis][offset + 1]
+  bool ok[3][3], low[3];
+  bool wall;
 };
-__device__ __forceinline__ int wrap1(int i, int n, int per) {
-  if (i >= 0 && i < n) return i;
-  if (!per) return -1;
-  return i < 0 ? i + n : i - n;
-}
 __device__ __forceinline__ Nbr neighbours(const cdesc* d, Ijk p) {
   Nbr b;
-  const int q[3] = {p.i, p.j, p.k}, n[3] = {d->nx, d->ny, d->nz};
+  const int q[3] = {p.i, p.j, p.k}, n[3] = {d->nx, d->ny, d->nz}, s[3] = {1, d->px, d->plane};
+  b.wall = false;
 #pragma unroll
-  for (int a = 0; a < 3; ++a)
-#pragma unroll
-    for (int o = 0; o < 3; ++o) b.c[a][o] = wrap1(q[a] + o - 1, n[a], d->per[a]);
+  for (int a = 0; a < 3; ++a) {
+    const bool lo = q[a] == 0, hi = q[a] == n[a] - 1, pec = !d->per[a];
+    const int span = (n[a] - 1) * s[a];
+    b.d[a][0] = lo ? (pec ? 0 : span) : -s[a];
+    b.d[a][1] = 0;
+    b.d[a][2] = hi ? (pec ? 0 : -span) : s[a];
+    b.ok[a][0] = !(lo & pec);
+    b.ok[a][1] = true;
+    b.ok[a][2] = !(hi & pec);
+    b.low[a] = lo & pec;
+    b.wall = b.wall | ((lo | hi) & pec);
+  }
   return b;
 }
 // The cell at offsets u, v in {-1, 0, 1} along the two axes transverse to
-// component c ((c+1) mod 3, (c+2) mod 3), or -1 beyond a PEC wall; *held: the
-// cell's component-c edge lies on a PEC wall (index 0 of a non-periodic
-// transverse axis) and is held at zero.
-__device__ __forceinline__ int nb_cell(const cdesc* d, const Nbr& b, int c, int u, int v, bool* held) {
-  const int a1 = (c + 1) % 3, a2 = (c + 2) % 3;
-  int o[3] = {1, 1, 1};
-  o[a1] += u;
-  o[a2] += v;
-  const int x = b.c[0][o[0]], y = b.c[1][o[1]], z = b.c[2][o[2]];
-  // bitwise, not short-circuit, operators: lane values must not become branches
-  *held = ((!d->per[a1]) & (b.c[a1][o[a1]] == 0)) | ((!d->per[a2]) & (b.c[a2][o[a2]] == 0));
-  return ((x | y | z) < 0) ? -1 : (z * d->ny + y) * d->px + x;
+// component c ((c+1) mod 3, (c+2) mod 3): its offset, and whether it exists.
+__device__ __forceinline__ int nb_off(const Nbr& b, int c, int u, int v) {
+  return b.d[(c + 1) % 3][u + 1] + b.d[(c + 2) % 3][v + 1];
+}
+__device__ __forceinline__ bool nb_ok(const Nbr& b, int c, int u, int v) {
+  return b.ok[(c + 1) % 3][u + 1] & b.ok[(c + 2) % 3][v + 1];
+}
+// That cell's component-c edge lies on a PEC wall (index 0 of a non-periodic
+// transverse axis) and is held at zero; u, v in {0, 1}: only the cell itself can
+// have index 0 along an axis it is not stepped along (or that it wraps around,
+// which a PEC axis does not).
+__device__ __forceinline__ bool nb_held(const Nbr& b, int c, int u, int v) {
+  return (u == 0 && b.low[(c + 1) % 3]) | (v == 0 && b.low[(c + 2) % 3]);
 }
 
 // A gain cell's state (populations as (hi, lo) FP32 pairs, coherences), its
@@ -1589,22 +1626,30 @@ struct DmCell {
   float Pn[3], dJ[3];
 };
 
-__device__ __forceinline__ void dm_load(const cdesc* d, const DmMats& sm, uint32_t g, long long n, DmCell& z) {
+// The cell and state of gain ordinal g (issued before the material table is
+// waited for), then what needs the table.
+__device__ __forceinline__ void dm_load_state(const cdesc* d, uint32_t g, DmCell& z) {
   const size_t ncs = (size_t)d->ncell;
   const gf* pop = G((const float*)d->pop);
+  auto state = [&](int q) { return R32<const float>{pop + (size_t)q * ncs}[g]; };
   z.g = g;
-  z.o = ((const __attribute__((address_space(1))) uint32_t*)d->glist)[g];
+  z.o = R32<const uint32_t>{(const __attribute__((address_space(1))) uint32_t*)d->glist}[g];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    z.nh[q] = state(q);
+    z.nl[q] = state(3 + q);
+    z.c[q] = {state(6 + q), state(9 + q)};
+    z.x[q] = {state(12 + q), state(15 + q)};
+  }
+}
+__device__ __forceinline__ void dm_load_medium(const cdesc* d, const DmMats& sm, long long n, DmCell& z) {
   z.p = ijk_of(d, z.o);
-  z.mt = &sm.m[((const gu8*)d->mat)[z.o]];
+  z.mt = &sm.m[R32<const uint8_t>{(const gu8*)d->mat}[z.o]];
   const fd_mat& mt = *z.mt;
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
-    z.nh[q] = pop[(size_t)q * ncs + g];
-    z.nl[q] = pop[(size_t)(3 + q) * ncs + g];
     z.pp[q] = z.nh[q] + z.nl[q];
     z.inc[q] = 0.0f;
-    z.c[q] = {pop[(size_t)(6 + q) * ncs + g], pop[(size_t)(9 + q) * ncs + g]};
-    z.x[q] = {pop[(size_t)(12 + q) * ncs + g], pop[(size_t)(15 + q) * ncs + g]};
     z.Pn[q] = mt.bk2 * z.c[q].r;
     z.dJ[q] = 0.0f;
   }
@@ -1618,175 +1663,190 @@ __device__ __forceinline__ void dm_load(const cdesc* d, const DmMats& sm, uint32
   }
 }
 
-// Gathers are branch-free: an index beyond a PEC wall (-1) reads cell 0 and the
-// value is replaced by 0 where it is used, so a thread's loads go out together
-// and are waited for once (a load under a branch is waited for on its own).
-__device__ __forceinline__ uint32_t clamp0(int e) { return e >= 0 ? (uint32_t)e : 0u; }
+// Gathers are branch-free within a wave: a neighbour beyond a PEC wall has offset
+// 0 and its value is replaced by 0 where it is used, so a thread's loads go out
+// together and are waited for once (a load under a lane's branch is waited for on
+// its own).  Waves without a cell at a wall (WALL = false) leave those tests out.
+__device__ __forceinline__ R32<const float> comp(const float* p) { return R32<const float>{G(p)}; }
 
-__global__ __launch_bounds__(FD_DM_CELLS) void dm_predict_kernel(const fd_dm_unit* __restrict__ units, int s) {
-  __shared__ DmMats sm;
-  const fd_dm_unit u = units[blockIdx.x];
-  const cdesc* d = (const cdesc*)u.d;
-  dm_stage_mats(d, sm);
-  if ((int)threadIdx.x >= u.count) return;
-  const long long n = d->step + s;
-  const int par = (int)(n & 1);
-  DmCell z;
-  dm_load(d, sm, (uint32_t)(u.first + (int)threadIdx.x), n, z);
-  const Nbr b = neighbours(d, z.p);
-  float em[3];
+template <bool WALL>
+__device__ __forceinline__ void dm_centre_pred(const cdesc* d, const Nbr& b, uint32_t o, int par, float em[3]) {
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
     // <(E^n + A)/2>: the cell's four component-q edges sit at offsets {0, 1}
-    const gf* En = G((const float*)d->E[par][q]);
-    const gf* A = G((const float*)d->E[par ^ 1][q]);
+    const R32<const float> En = comp(d->E[par][q]), A = comp(d->E[par ^ 1][q]);
     float acc = 0.0f;
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
-        bool held;
-        const int e = nb_cell(d, b, q, a, c, &held);
-        const uint32_t ec = clamp0(e);
-        const float v = En[ec] + A[ec];
-        acc += e >= 0 ? v : 0.0f;
+        const uint32_t e = o + nb_off(b, q, a, c);
+        const float v = En[e] + A[e];
+        acc += !WALL || nb_ok(b, q, a, c) ? v : 0.0f;
       }
     em[q] = 0.125f * acc;
   }
+}
+
+__global__ __launch_bounds__(FD_DM_CELLS) void dm_predict_kernel(const fd_dm_unit* __restrict__ units, int s) {
+  __shared__ DmMats sm;
+  const fd_dm_unit u = units[dm_unit((int)blockIdx.x, (int)gridDim.x)];
+  const cdesc* d = (const cdesc*)u.d;
+  const long long n = d->step + s;
+  const int par = (int)(n & 1), t = (int)threadIdx.x;
+  DmCell z;
+  dm_stage_mats(d, sm, [&] { dm_load_state(d, (uint32_t)(u.first + (t < u.count ? t : 0)), z); });
+  if (t >= u.count) return;
+  dm_load_medium(d, sm, n, z);
+  const Nbr b = neighbours(d, z.p);
+  float em[3];
+  if (__any(b.wall)) dm_centre_pred<true>(d, b, z.o, par, em);
+  else dm_centre_pred<false>(d, b, z.o, par, em);
   dm_relax(*z.mt, z.pp, z.inc, z.c, z.x);
   dm_cayley<false>(*z.mt, em, z.pp, z.inc, z.c, z.x);
   gf* Q = G(d->dmq[0]);
   const size_t ncs = (size_t)d->ncell;
 #pragma unroll
-  for (int q = 0; q < 3; ++q) Q[(size_t)q * ncs + z.o] = z.mt->bk2 * (z.c[q].r * z.mt->bf2) - z.Pn[q] + z.dJ[q];
+  for (int q = 0; q < 3; ++q)
+    R32<float>{Q + (size_t)q * ncs}[z.o] = z.mt->bk2 * (z.c[q].r * z.mt->bf2) - z.Pn[q] + z.dJ[q];
 }
 
-__global__ __launch_bounds__(FD_DM_CELLS) void dm_correct_kernel(const fd_dm_unit* __restrict__ units, int s) {
-  __shared__ DmMats sm;
-  const fd_dm_unit u = units[blockIdx.x];
-  const cdesc* d = (const cdesc*)u.d;
-  dm_stage_mats(d, sm);
-  if ((int)threadIdx.x >= u.count) return;
-  const long long n = d->step + s;
-  const int par = (int)(n & 1);
-  DmCell z;
-  dm_load(d, sm, (uint32_t)(u.first + (int)threadIdx.x), n, z);
-  const Nbr b = neighbours(d, z.p);
-  const gf* Qs = G((const float*)d->dmq[0]);
-  const gu8* map = (const gu8*)d->mat;
+template <bool WALL>
+__device__ __forceinline__ void dm_centre_corr(const cdesc* d, const DmMats& sm, const Nbr& b, uint32_t o, int par,
+                                               float em[3]) {
+  const R32<const uint8_t> map{(const gu8*)d->mat};
   const size_t ncs = (size_t)d->ncell;
-  float em[3];
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
     // Q* of the 3 x 3 cells around the centre across component q (0 off the
-    // grid; cells without gain hold 0), and the voxels of the cell's four edges
+    // grid; cells without gain hold 0)
+    const R32<const float> Qs = comp(d->dmq[0] + (size_t)q * ncs);
     float qn[3][3];
-    int ee[2][2];
-    bool he[2][2];
-    uint32_t me[2][2];
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        bool held;
-        const int e = nb_cell(d, b, q, a - 1, c - 1, &held);
-        const float v = Qs[(size_t)q * ncs + clamp0(e)];
-        qn[a][c] = e >= 0 ? v : 0.0f;
-        if (a >= 1 && c >= 1) {
-          ee[a - 1][c - 1] = e;
-          he[a - 1][c - 1] = held;
-          me[a - 1][c - 1] = map[clamp0(e)];
-        }
+        const float v = Qs[o + nb_off(b, q, a - 1, c - 1)];
+        qn[a][c] = !WALL || nb_ok(b, q, a - 1, c - 1) ? v : 0.0f;
       }
     // <E^n + E*> with E* = A - [Q*]/eps on the edges (0 beyond or on a PEC wall);
     // the edge at offsets (a, c) is shared by the cells at (a - 1 .. a, c - 1 .. c)
-    const gf* En = G((const float*)d->E[par][q]);
-    const gf* A = G((const float*)d->E[par ^ 1][q]);
+    const R32<const float> En = comp(d->E[par][q]), A = comp(d->E[par ^ 1][q]);
     float acc = 0.0f;
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
-        const int e = ee[a][c];
-        const uint32_t ec = clamp0(e);
-        const float en = En[ec], av = A[ec];
+        const uint32_t e = o + nb_off(b, q, a, c);
+        const float en = En[e], av = A[e];
         const float sh = 0.25f * ((qn[a][c] + qn[a + 1][c]) + (qn[a][c + 1] + qn[a + 1][c + 1]));
-        const float es = av - sh * sm.m[me[a][c]].inv_eps;
-        acc += e >= 0 ? en : 0.0f;
-        acc += ((e >= 0) & !he[a][c]) ? es : 0.0f;
+        const float es = av - sh * sm.m[map[e]].inv_eps;
+        const bool ok = !WALL || nb_ok(b, q, a, c);
+        acc += ok ? en : 0.0f;
+        acc += !WALL || (ok & !nb_held(b, q, a, c)) ? es : 0.0f;
       }
     em[q] = 0.125f * acc;
   }
+}
+
+__global__ __launch_bounds__(FD_DM_CELLS) void dm_correct_kernel(const fd_dm_unit* __restrict__ units, int s) {
+  __shared__ DmMats sm;
+  const fd_dm_unit u = units[dm_unit((int)blockIdx.x, (int)gridDim.x)];
+  const cdesc* d = (const cdesc*)u.d;
+  const long long n = d->step + s;
+  const int par = (int)(n & 1), t = (int)threadIdx.x;
+  DmCell z;
+  dm_stage_mats(d, sm, [&] { dm_load_state(d, (uint32_t)(u.first + (t < u.count ? t : 0)), z); });
+  if (t >= u.count) return;
+  dm_load_medium(d, sm, n, z);
+  const Nbr b = neighbours(d, z.p);
+  const size_t ncs = (size_t)d->ncell;
+  float em[3];
+  if (__any(b.wall)) dm_centre_corr<true>(d, sm, b, z.o, par, em);
+  else dm_centre_corr<false>(d, sm, b, z.o, par, em);
   dm_relax(*z.mt, z.pp, z.inc, z.c, z.x);
   dm_cayley<true>(*z.mt, em, z.pp, z.inc, z.c, z.x);
   dm_relax(*z.mt, z.pp, z.inc, z.c, z.x);
   gf* pop = G(d->pop);
   gf* Q = G(d->dmq[1]);
+  auto put = [&](int q, float v) { R32<float>{pop + (size_t)q * ncs}[z.g] = v; };
 #pragma unroll
   for (int r = 0; r < 3; ++r) {
-    Q[(size_t)r * ncs + z.o] = z.mt->bk2 * z.c[r].r - z.Pn[r] + z.dJ[r];
+    R32<float>{Q + (size_t)r * ncs}[z.o] = z.mt->bk2 * z.c[r].r - z.Pn[r] + z.dJ[r];
     two_sum(z.nh[r], z.nl[r], z.inc[r]);
-    pop[(size_t)r * ncs + z.g] = z.nh[r];
-    pop[(size_t)(3 + r) * ncs + z.g] = z.nl[r];
-    pop[(size_t)(6 + r) * ncs + z.g] = z.c[r].r;
-    pop[(size_t)(9 + r) * ncs + z.g] = z.c[r].i;
-    pop[(size_t)(12 + r) * ncs + z.g] = z.x[r].r;
-    pop[(size_t)(15 + r) * ncs + z.g] = z.x[r].i;
+    put(r, z.nh[r]);
+    put(3 + r, z.nl[r]);
+    put(6 + r, z.c[r].r);
+    put(9 + r, z.c[r].i);
+    put(12 + r, z.x[r].r);
+    put(15 + r, z.x[r].i);
   }
 }
 
 // E^{n+1} = A - [Q]/eps on the edges next to gain cells, one listed cell per
 // thread (the cells whose edges a gain cell shares): the twelve Q values first
 // (cells without gain hold Q = 0), then, for a cell with a changed edge, its A
-// and the new E.
-__global__ __launch_bounds__(FD_DM_EDGES) void dm_edges_kernel(const fd_dm_unit* __restrict__ units, int s) {
-  __shared__ DmMats sm;
-  const fd_dm_unit u = units[blockIdx.x];
-  const cdesc* d = (const cdesc*)u.d;
-  dm_stage_mats(d, sm);
-  const int t = (int)threadIdx.x;
-  if (t >= u.count) return;
-  const long long n = d->step + s;
-  const int par = (int)(n & 1);
-  const gf* Q = G((const float*)d->dmq[1]);
+// and the new E; and the samples of the E probes in listed cells (u.probes), which
+// the step kernel recorded from A.
+template <bool WALL>
+__device__ __forceinline__ void dm_edge_sums(const cdesc* d, const Nbr& b, uint32_t o, float acc[3]) {
   const size_t ncs = (size_t)d->ncell;
-  const uint32_t o = ((const __attribute__((address_space(1))) uint32_t*)d->elist)[u.first + t];
-  const Nbr b = neighbours(d, ijk_of(d, o));
-  // the cell's A and material go out with the sharers' Q (one round trip)
-  float ev[3];
-#pragma unroll
-  for (int c = 0; c < 3; ++c) ev[c] = G((const float*)d->E[par ^ 1][c])[o];
-  const uint32_t mo = ((const gu8*)d->mat)[o];
-  float acc[3];
-  bool held[3];
-  bool any = false;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    (void)nb_cell(d, b, c, 0, 0, &held[c]);
     // the cells sharing the edge: offsets {0, -1} along the transverse axes
+    const R32<const float> Q = comp(d->dmq[1] + (size_t)c * ncs);
     acc[c] = 0.0f;
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
       for (int v = 0; v < 2; ++v) {
-        bool h2;
-        const int cc = nb_cell(d, b, c, -a, -v, &h2);
-        const float qv = Q[(size_t)c * ncs + clamp0(cc)];
-        acc[c] += cc >= 0 ? qv : 0.0f;
+        const float qv = Q[o + nb_off(b, c, -a, -v)];
+        acc[c] += !WALL || nb_ok(b, c, -a, -v) ? qv : 0.0f;
       }
-    any = any | (!held[c] & (acc[c] != 0.0f));
+    if (WALL && nb_held(b, c, 0, 0)) acc[c] = 0.0f;
   }
-  if (!any) return;
+}
+
+__global__ __launch_bounds__(FD_DM_EDGES) void dm_edges_kernel(const fd_dm_unit* __restrict__ units, int s) {
+  __shared__ DmMats sm;
+  const fd_dm_unit u = units[dm_unit((int)blockIdx.x, (int)gridDim.x)];
+  const cdesc* d = (const cdesc*)u.d;
+  const int t = (int)threadIdx.x;
+  const long long n = d->step + s;
+  const int par = (int)(n & 1);
+  uint32_t o;
+  dm_stage_mats(d, sm, [&] {
+    o = R32<const uint32_t>{(const __attribute__((address_space(1))) uint32_t*)d->elist}[u.first + (t < u.count ? t : 0)];
+  });
+  if (t >= u.count) return;
+  const Nbr b = neighbours(d, ijk_of(d, o));
+  // the cell's A and material go out with the sharers' Q (one round trip)
+  float ev[3], acc[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) ev[c] = comp(d->E[par ^ 1][c])[o];
+  const uint32_t mo = R32<const uint8_t>{(const gu8*)d->mat}[o];
+  if (__any(b.wall)) dm_edge_sums<true>(d, b, o, acc);
+  else dm_edge_sums<false>(d, b, o, acc);
   const float ie = sm.m[mo].inv_eps;
 #pragma unroll
   for (int c = 0; c < 3; ++c)
-    if (!held[c] && acc[c] != 0.0f) G(d->E[par ^ 1][c])[o] = ev[c] - 0.25f * acc[c] * ie;
+    if (acc[c] != 0.0f) {
+      ev[c] = ev[c] - 0.25f * acc[c] * ie;
+      R32<float>{G(d->E[par ^ 1][c])}[o] = ev[c];
+    }
+  for (unsigned mm = u.probes; mm; mm &= mm - 1u) {  // uniform
+    const int p = __builtin_ctz(mm), cp = d->probe_comp[p];
+    if ((uint32_t)(d->probe_k[p] * d->plane + d->probe_cell[p]) != o) continue;
+    float v = ev[2];
+    v = cp == 1 ? ev[1] : v;
+    v = cp == 0 ? ev[0] : v;
+    G(d->probe_ring)[(long long)p * d->max_steps + n] = v;
+  }
 }
 
-// After the edge pass: probe samples of E components and the T(t) partial of
-// every xy tile of a flux plane, recomputed from the final E^{n+1} (the step
-// kernels recorded them from A).  Unit: first = flux plane (-1: the probes),
-// count = xy tile; the block has the plan's tile shape.
+// After the edge pass: the T(t) partial of every xy tile of a flux plane,
+// recomputed from the final E^{n+1} (the step kernels recorded it from A).  Unit:
+// first = flux plane, count = xy tile; the block has the plan's tile shape.
 __global__ __launch_bounds__(FD_MAXBLOCK) void dm_diag_kernel(const fd_dm_unit* __restrict__ units, int s) {
   __shared__ double red[FD_MAXBLOCK / 64];
   const fd_dm_unit u = units[blockIdx.x];
@@ -1794,12 +1854,6 @@ __global__ __launch_bounds__(FD_MAXBLOCK) void dm_diag_kernel(const fd_dm_unit* 
   const long long n = d->step + s;
   const int par = (int)(n & 1);
   const int t = (int)threadIdx.x;
-  if (u.first < 0) {
-    if (t < d->nprobe && d->probe_comp[t] < 3)
-      G(d->probe_ring)[(long long)t * d->max_steps + n] =
-          G((const float*)d->E[par ^ 1][d->probe_comp[t]])[(size_t)d->probe_k[t] * d->plane + d->probe_cell[t]];
-    return;
-  }
   const int f = u.first, blk = u.count;
   const int TX = d->tile_x, TY = (int)blockDim.x / TX;
   const int ntx = (d->nx + TX - 1) / TX;
