@@ -94,7 +94,7 @@ def cpu_sample_config(workload, steps):
 def kernel_source_sha():
     import hashlib
     h = hashlib.sha256()
-    for name in ("kernels.hip", "fd_internal.h"):
+    for name in ("step.hip", "kernels.hip", "fd_device.h", "fd_internal.h"):
         with open(os.path.join(ROOT, "paper_0802_3775_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
@@ -201,9 +201,8 @@ def kernel_table(plan, nsteps):
     launch on the launch stream: the kernel's own begin and end timestamps) and
     the algorithmic bytes of one launch (libfdtd counts them per cell: 49 B, +32 B
     per CPML slab axis, +84 B per Lorentz or +144 B per density-matrix gain cell,
-    +4 B per cell of a gain tile for its gain ordinal; a DFT launch stores a
-    40 B/point plane sample and, once per 32-sample ring, moves 128 B per plane
-    point and frequency: averaged per launch)."""
+    +4 B per cell of a gain tile for its gain ordinal; a DFT launch, once per ring of
+    32 samples, moves 128 B per plane point and frequency and reads the ring)."""
     from paper_0802_3775_amd import fdtd
     ms, cnt = plan.time_kernels(nsteps)
     cells = plan.class_cells()

@@ -10,12 +10,15 @@ import os
 import subprocess
 import sys
 import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libfdtd.so")
-SOURCES = ["kernels.hip", "api.cpp", "geometry.cpp"]
+# (source, extra flags): the step kernels are one file compiled for each tile width
+SOURCES = [("step.hip", ["-DFD_STEP_TX=16"]), ("step.hip", ["-DFD_STEP_TX=32"]), ("step.hip", ["-DFD_STEP_TX=64"]),
+           ("kernels.hip", []), ("api.cpp", []), ("geometry.cpp", [])]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-ffp-contract=off", "-Wall",
@@ -26,15 +29,18 @@ HOST = ["-x", "c++", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include"]
 
 def build(verbose: bool = False) -> str:
     with tempfile.TemporaryDirectory(prefix="fdtd_build_") as tmp:
-        objs = []
-        for src in SOURCES:
-            obj = os.path.join(tmp, src + ".o")
-            cmd = [HIPCC] + COMMON + (DEVICE if src.endswith(".hip") else HOST) + \
+        def compile_one(at):
+            src, flags = SOURCES[at]
+            obj = os.path.join(tmp, "%d_%s.o" % (at, src))
+            cmd = [HIPCC] + COMMON + (DEVICE if src.endswith(".hip") else HOST) + flags + \
                   ["-c", os.path.join(CSRC, src), "-o", obj]
             if verbose:
                 print(" ".join(cmd), flush=True)
             subprocess.run(cmd, check=True)
-            objs.append(obj)
+            return obj
+
+        with ThreadPoolExecutor(4) as pool:
+            objs = list(pool.map(compile_one, range(len(SOURCES))))
         cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB + ".tmp"] + objs
         if verbose:
             print(" ".join(cmd), flush=True)

@@ -106,6 +106,70 @@ struct Fork {
   }
 };
 
+// The captured graphs of a plan or batch by their number of steps: graph_steps,
+// and up to kOther other lengths that came up twice.
+struct Graphs {
+  static constexpr size_t kOther = 8;
+  static constexpr int64_t kShortest = 4;  // launches fewer than these go out one by one
+  std::map<int64_t, GraphEntry> by_len;
+  std::map<int64_t, int> seen;
+  hipStream_t cap = nullptr;
+  std::unique_ptr<Fork> fork;
+  void drop() {
+    for (auto& kv : by_len) {
+      if (kv.second.exec) (void)hipGraphExecDestroy(kv.second.exec);
+      if (kv.second.graph) (void)hipGraphDestroy(kv.second.graph);
+    }
+    by_len.clear();
+    seen.clear();
+  }
+  ~Graphs() {
+    drop();
+    if (cap) (void)hipStreamDestroy(cap);
+  }
+  // Launches a graph of the first steps of a run of *n steps on st, if there is
+  // one for it (captured here through enqueue(steps, stream, fork) when it is
+  // due): *n is then its length and *done true.  Otherwise *n is unchanged.
+  template <class Enqueue>
+  int launch(int64_t K, int parallel, int64_t* n, hipStream_t st, Enqueue&& enqueue, bool* done) {
+    *done = false;
+    if (K <= 0 || *n < std::min(K, kShortest)) return FDTD_OK;
+    const int64_t len = std::min(*n, K);
+    auto it = by_len.find(len);
+    if (it == by_len.end()) {
+      if (len != K) {
+        if (by_len.size() > kOther) return FDTD_OK;
+        if (seen.size() > 64) seen.clear();
+        if (++seen[len] < 2) return FDTD_OK;
+      }
+      if (!cap) HIPCHK(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
+      Fork* fk = nullptr;
+      if (parallel) {
+        if (!fork) fork.reset(new Fork());
+        if (int rf = fork->init()) return rf;
+        fk = fork.get();
+      }
+      GraphEntry ge;
+      HIPCHK(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
+      const int r = enqueue(len, cap, fk);
+      hipGraph_t gr = nullptr;
+      const hipError_t e = hipStreamEndCapture(cap, &gr);
+      if (r) {
+        if (gr) (void)hipGraphDestroy(gr);
+        return r;
+      }
+      if (e != hipSuccess) return fail(FDTD_EHIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
+      ge.graph = gr;
+      HIPCHK(hipGraphInstantiate(&ge.exec, gr, nullptr, nullptr, 0));
+      it = by_len.emplace(len, ge).first;
+    }
+    HIPCHK(hipGraphLaunch(it->second.exec, st));
+    *n = len;
+    *done = true;
+    return FDTD_OK;
+  }
+};
+
 // Split a tile list into 8 contiguous parts of about equal cost, one per XCD;
 // *grid = 8 x the longest part (the kernel's workgroup count).
 fd_xcd xcd_partition(const std::vector<double>& cost, int* grid) {
@@ -136,6 +200,7 @@ struct TileSet {
   std::vector<double> cost[FD_NCLASS];
   fd_xcd part[FD_NCLASS] = {};
   int pgrid[FD_NCLASS] = {};
+  int nflux[FD_NCLASS] = {};  // the most flux planes a tile has
   fd_tile* dev[FD_NCLASS] = {};
 };
 
@@ -187,9 +252,7 @@ struct fdtd_plan {
   int src_len[FD_MAXSRC] = {0, 0, 0, 0};
   bool has_gain = false;
   int gm = 0;  // gain model of the plan's gain materials: 0 none, 1 Lorentz, 2 density matrix
-  hipStream_t cap = nullptr;
-  std::unique_ptr<Fork> fork;
-  std::map<int64_t, GraphEntry> graphs;
+  Graphs graphs;
 };
 
 // Members [m0, m1) of a batch, stepped together: their sub-ranges of the
@@ -200,6 +263,7 @@ struct BGroup {
   int t0[FD_NCLASS] = {}, nt[FD_NCLASS] = {};
   fd_xcd part[FD_NCLASS] = {};
   int pgrid[FD_NCLASS] = {};
+  int nflux[FD_NCLASS] = {};
   int d0 = 0, nd = 0;
   int u0[3] = {}, nu[3] = {};
   int maxnf = 0;
@@ -229,9 +293,7 @@ struct fdtd_batch {
   fd_tile* dtiles[FD_NCLASS] = {};
   fd_dft_tile* ddft = nullptr;
   fd_desc** ddescs = nullptr;
-  hipStream_t cap = nullptr;
-  std::unique_ptr<Fork> fork;
-  std::map<std::vector<int64_t>, GraphEntry> graphs;
+  Graphs graphs;
 };
 
 namespace {
@@ -764,7 +826,7 @@ struct DmLaunch {
 };
 
 int enqueue_step(fd_tile* const dtiles[FD_NCLASS], const int* ntiles, const fd_xcd* part,
-                 const int* pgrid, int tile_x, int block, int max_blocks, const fd_dft_tile* ddft, int ndft,
+                 const int* pgrid, const int* nflux, int tile_x, int block, int max_blocks, const fd_dft_tile* ddft, int ndft,
                  int maxnf, bool dft_due, int s, int ntst, const DmLaunch& dm, hipStream_t st, Fork* fk) {
   int used[FD_NCLASS], nused = 0;
   for (int c = 0; c < FD_NCLASS; ++c)
@@ -781,7 +843,7 @@ int enqueue_step(fd_tile* const dtiles[FD_NCLASS], const int* ntiles, const fd_x
       on = fk->side[c];
       HIPCHK(hipStreamWaitEvent(on, fk->fork, 0));
     }
-    HIPCHK(fd_launch_step(c, dtiles[c], nt, tile_x, block, grid, s, pc, ntst, on));
+    HIPCHK(fd_launch_step(c, dtiles[c], nt, tile_x, block, grid, s, pc, ntst, nflux[c], on));
     if (par && u > 0) HIPCHK(hipEventRecord(fk->join[c], on));
   }
   if (par)
@@ -803,26 +865,41 @@ DmLaunch plan_dm(const fdtd_plan* p) {
   return l;
 }
 
-bool plan_dft_due(const fdtd_plan* p, int64_t n) {
+// First step >= n whose sample fills the ring of a flux plane: the DFT launch
+// follows it (a step past every run if the plan has no spectra).
+int64_t next_flush(const fdtd_plan* p, int64_t n) {
+  int64_t best = INT64_MAX;
+  for (const Flux& f : p->flux) {
+    if (f.nf == 0) continue;
+    const int64_t period = (int64_t)f.decim * FD_DFT_RING, last = (int64_t)f.decim * (FD_DFT_RING - 1);
+    best = std::min(best, n <= last ? last : last + (n - last + period - 1) / period * period);
+  }
+  return best;
+}
+
+// In a graph that the caller captures, a DFT launch follows every sampled step, as
+// the replays may come to a full ring at any of them (the kernel looks).
+bool plan_dft_due(const fdtd_plan* p, int64_t n, bool captured) {
+  if (!captured) return next_flush(p, n) == n;
   for (const Flux& f : p->flux)
     if (f.nf > 0 && n % f.decim == 0) return true;
   return false;
 }
 
-int64_t plan_phase_key(const fdtd_plan* p, int64_t n0) {
-  int64_t l = 1;
-  for (const Flux& f : p->flux)
-    if (f.nf > 0) l = std::lcm(l, (int64_t)f.decim);
-  return n0 % l;
+bool caller_captures(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &status) == hipSuccess) return status == hipStreamCaptureStatusActive;
+  (void)hipGetLastError();
+  return false;
 }
 
-int plan_enqueue(fdtd_plan* p, int64_t n, hipStream_t st, Fork* fk) {
+int plan_enqueue(fdtd_plan* p, int64_t n, hipStream_t st, Fork* fk, bool captured = false) {
   int nt[FD_NCLASS];
   for (int c = 0; c < FD_NCLASS; ++c) nt[c] = (int)p->own.tiles[c].size();
   for (int64_t s = 0; s < n; ++s) {
-    const int r = enqueue_step(p->own.dev, nt, p->own.part, p->own.pgrid, p->tune.tile_x, p->tune.block,
+    const int r = enqueue_step(p->own.dev, nt, p->own.part, p->own.pgrid, p->own.nflux, p->tune.tile_x, p->tune.block,
                                p->tune.max_blocks, p->ddft, (int)p->dft.size(), p->maxnf,
-                               plan_dft_due(p, p->step + s), (int)s, p->ntst, plan_dm(p), st, fk);
+                               plan_dft_due(p, p->step + s, captured), (int)s, p->ntst, plan_dm(p), st, fk);
     if (r) return r;
   }
   HIPCHK(fd_launch_advance_one(p->ddesc, n, st));
@@ -880,11 +957,6 @@ int fdtd_plan_create(const fdtd_grid_desc* g, fdtd_plan** out) {
 
 void fdtd_plan_destroy(fdtd_plan* p) {
   if (!p) return;
-  for (auto& kv : p->graphs) {
-    if (kv.second.exec) (void)hipGraphExecDestroy(kv.second.exec);
-    if (kv.second.graph) (void)hipGraphDestroy(kv.second.graph);
-  }
-  if (p->cap) (void)hipStreamDestroy(p->cap);
   delete p;
 }
 
@@ -1226,6 +1298,7 @@ int fdtd_bind_arena(fdtd_plan* p, void* dev, size_t bytes, int64_t max_steps, vo
     d.flux_T[f] = at<double>(p, L.fluxT[f]);
     d.flux_nf[f] = fl.nf;
     d.flux_decim[f] = fl.decim;
+    divisor((uint32_t)fl.decim, d.div_decim[f]);
     d.flux_f[f] = at<double>(p, L.fluxf[f]);
     d.flux_acc[f] = at<double>(p, L.fluxacc[f]);
     d.flux_ring[f] = fl.nf > 0 ? at<float>(p, L.fluxring[f]) : nullptr;
@@ -1252,6 +1325,7 @@ int fdtd_bind_arena(fdtd_plan* p, void* dev, size_t bytes, int64_t max_steps, vo
     p->maxnf = std::max(p->maxnf, fl.nf);
   }
   d.ke = p->ke;
+  divisor((uint32_t)std::max(1, p->ke), d.div_ke);
   d.ntiles = p->ntiles;
   d.energy = p->ke > 0 ? at<double>(p, L.energy) : nullptr;
   d.dt = p->dt;
@@ -1364,7 +1438,7 @@ int fdtd_bind_arena(fdtd_plan* p, void* dev, size_t bytes, int64_t max_steps, vo
         t.k0 = ch.first;
         t.k1 = ch.second;
         t.tidx = slot ? (*slot)++ : 0;
-        t.flags = flags;
+        t.flags = flags | (p->ke > 0 ? FD_TILE_KE : 0);
         t.blk = by * ntx + bx;
         // sources, probes and flux planes the tile's kernel must look at
         for (int q = 0; q < d.nsrc; ++q) {
@@ -1429,6 +1503,8 @@ int fdtd_bind_arena(fdtd_plan* p, void* dev, size_t bytes, int64_t max_steps, vo
       }
       ts.tiles[pml + 3 * gain].push_back(all[q]);
       ts.cost[pml + 3 * gain].push_back(tcost[q]);
+      int& nf = ts.nflux[pml + 3 * gain];
+      nf = std::max(nf, __builtin_popcount(all[q].fmask));
     }
     for (int c = 0; c < FD_NCLASS; ++c) {
       ts.part[c] = xcd_partition(ts.cost[c], &ts.pgrid[c]);
@@ -1496,46 +1572,30 @@ int fdtd_get_material_map(fdtd_plan* p, uint8_t* host_map, void* stream) {
   return FDTD_OK;
 }
 
+// Steps are enqueued in runs that end with a DFT launch (next_flush): a run's steps
+// without one are the same launches at any step, so one graph of graph_steps steps
+// serves them all, and what is left of a run goes out as a graph of its own length
+// when that length comes up again.
 static int plan_step(fdtd_plan* p, int64_t n, hipStream_t st) {
   if (n < 0) return fail(FDTD_EINVAL, "negative step count");
   if (p->step + n > p->max_steps) return fail(FDTD_ESTATE, "max_steps (%lld) exceeded", (long long)p->max_steps);
-  const int64_t K = p->tune.graph_steps;
-  int64_t done = 0;
-  if (K > 0) {
-    while (n - done >= K) {
-      const int64_t key = plan_phase_key(p, p->step) * 1000003 + K;
-      auto it = p->graphs.find(key);
-      if (it == p->graphs.end()) {
-        if (!p->cap) HIPCHK(hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking));
-        Fork* fk = nullptr;
-        if (p->tune.parallel) {
-          if (!p->fork) p->fork.reset(new Fork());
-          if (int rf = p->fork->init()) return rf;
-          fk = p->fork.get();
-        }
-        GraphEntry ge;
-        HIPCHK(hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal));
-        const int r = plan_enqueue(p, K, p->cap, fk);
-        hipGraph_t gr = nullptr;
-        const hipError_t e = hipStreamEndCapture(p->cap, &gr);
-        if (r) {
-          if (gr) (void)hipGraphDestroy(gr);
-          return r;
-        }
-        if (e != hipSuccess) return fail(FDTD_EHIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
-        ge.graph = gr;
-        HIPCHK(hipGraphInstantiate(&ge.exec, gr, nullptr, nullptr, 0));
-        it = p->graphs.emplace(key, ge).first;
-      }
-      HIPCHK(hipGraphLaunch(it->second.exec, st));
-      p->step += K;
-      done += K;
-    }
+  if (n > 0 && caller_captures(st)) {
+    if (int r = plan_enqueue(p, n, st, nullptr, true)) return r;
+    p->step += n;
+    return FDTD_OK;
   }
-  if (n - done > 0) {
-    const int r = plan_enqueue(p, n - done, st, nullptr);
-    if (r) return r;
-    p->step += n - done;
+  Graphs& g = p->graphs;
+  auto enqueue = [&](int64_t k, hipStream_t on, Fork* fk) { return plan_enqueue(p, k, on, fk); };
+  for (int64_t done = 0; done < n;) {
+    int64_t k = std::min(n - done, next_flush(p, p->step) - p->step);  // steps without a DFT launch
+    bool graphed = false;
+    if (int r = g.launch(p->tune.graph_steps, p->tune.parallel, &k, st, enqueue, &graphed)) return r;
+    if (!graphed) {  // with the DFT launch, if the run's end is reached
+      k = std::min(n - done, k + 1);
+      if (int r = plan_enqueue(p, k, st, nullptr)) return r;
+    }
+    p->step += k;
+    done += k;
   }
   return FDTD_OK;
 }
@@ -1786,11 +1846,10 @@ int fdtd_class_bytes(const fdtd_plan* p, double* bytes) {
           }
     bytes[c] = acc;
   }
-  // per DFT launch: the sample (24 bytes read, 16 written per point), and once
-  // per ring the accumulators (128 bytes per point and frequency) and the ring
+  // per DFT launch: the accumulators (128 bytes per point and frequency) and the ring
   double dft = 0.0;
   for (const Flux& f : p->flux)
-    if (f.nf > 0) dft += (double)nx * ny * (40.0 + (128.0 * f.nf + 16.0 * FD_DFT_RING) / FD_DFT_RING);
+    if (f.nf > 0) dft += (double)nx * ny * (128.0 * f.nf + 16.0 * FD_DFT_RING);
   bytes[FD_KERNEL_DFT] = dft;
   for (int q = 0; q < 4; ++q) bytes[FD_KERNEL_DM + q] = p->dm_bytes[q];
   return FDTD_OK;
@@ -1829,12 +1888,13 @@ int fdtd_time_kernels(fdtd_plan* p, int64_t n, void* stream, double* ms, int64_t
       const int grid = p->tune.max_blocks > 0 ? std::min(nt, p->tune.max_blocks) : p->own.pgrid[c];
       const fd_xcd* pc = p->tune.max_blocks > 0 ? nullptr : &p->own.part[c];
       const int r = record(c, [&](hipEvent_t a, hipEvent_t b) {
-        return fd_launch_step(c, p->own.dev[c], nt, p->tune.tile_x, p->tune.block, grid, (int)s, pc, p->ntst, st, a,
+        return fd_launch_step(c, p->own.dev[c], nt, p->tune.tile_x, p->tune.block, grid, (int)s, pc, p->ntst,
+                              p->own.nflux[c], st, a,
                               b);
       });
       if (r) { cleanup(); return r; }
     }
-    if (plan_dft_due(p, p->step + s) && !p->dft.empty()) {
+    if (next_flush(p, p->step + s) == p->step + s) {
       const int r = record(FD_KERNEL_DFT, [&](hipEvent_t a, hipEvent_t b) {
         return fd_launch_dft(p->ddft, (int)p->dft.size(), (int)s, st, a, b);
       });
@@ -2037,6 +2097,7 @@ void batch_layout(fdtd_batch* b, fdtd_plan* const* plans, int32_t n, int gm) {
     for (int c = 0; c < FD_NCLASS; ++c) {
       b->tiles[c].insert(b->tiles[c].end(), p->ts.tiles[c].begin(), p->ts.tiles[c].end());
       gcost[c].insert(gcost[c].end(), p->ts.cost[c].begin(), p->ts.cost[c].end());
+      g.nflux[c] = std::max(g.nflux[c], p->ts.nflux[c]);
     }
     b->dft.insert(b->dft.end(), p->dft.begin(), p->dft.end());
     b->maxnf = std::max(b->maxnf, p->maxnf);
@@ -2062,14 +2123,6 @@ size_t batch_table_bytes(const fdtd_batch* b, size_t off_t[FD_NCLASS], size_t* o
   }
   *off_p = bytes;
   return align256(bytes + sizeof(fd_desc*) * b->plans.size());
-}
-
-void batch_drop_graphs(fdtd_batch* b) {
-  for (auto& kv : b->graphs) {
-    if (kv.second.exec) (void)hipGraphExecDestroy(kv.second.exec);
-    if (kv.second.graph) (void)hipGraphDestroy(kv.second.graph);
-  }
-  b->graphs.clear();
 }
 
 // Writes the launch tables of b's members to b->dmem (b->dcap bytes, the
@@ -2204,22 +2257,20 @@ int fdtd_batch_set_members(fdtd_batch* b, fdtd_plan* const* plans, int32_t n, vo
     b->dmem = grown;
     b->dcap = bytes + bytes / 2;
   }
-  batch_drop_graphs(b);
+  b->graphs.drop();
   batch_layout(b, plans, n, gm);
   return batch_upload(b);
 }
 
 void fdtd_batch_destroy(fdtd_batch* b) {
   if (!b) return;
-  batch_drop_graphs(b);
-  if (b->cap) (void)hipStreamDestroy(b->cap);
   if (b->dmem && b->owns_dmem) (void)hipFree(b->dmem);
   delete b;
 }
 
-static bool group_dft_due(const fdtd_batch* b, const BGroup& g, int64_t s) {
+static bool group_dft_due(const fdtd_batch* b, const BGroup& g, int64_t s, bool captured) {
   for (int m = g.m0; m < g.m1; ++m)
-    if (plan_dft_due(b->plans[m], b->plans[m]->step + s)) return true;
+    if (plan_dft_due(b->plans[m], b->plans[m]->step + s, captured)) return true;
   return false;
 }
 
@@ -2235,14 +2286,14 @@ static DmLaunch group_dm(const fdtd_batch* b, const BGroup& g) {
 // n steps of every member, group after group (a group's state stays in the
 // Infinity Cache over its n steps when it fits there); members are independent,
 // so the order changes no result.
-static int batch_enqueue(fdtd_batch* b, int64_t n, hipStream_t st, Fork* fk) {
+static int batch_enqueue(fdtd_batch* b, int64_t n, hipStream_t st, Fork* fk, bool captured = false) {
   for (const BGroup& g : b->groups) {
     fd_tile* dt[FD_NCLASS];
     for (int c = 0; c < FD_NCLASS; ++c) dt[c] = b->dtiles[c] + g.t0[c];
     const DmLaunch dm = group_dm(b, g);
     for (int64_t s = 0; s < n; ++s) {
-      const int r = enqueue_step(dt, g.nt, g.part, g.pgrid, b->tile_x, b->block, b->max_blocks, b->ddft + g.d0, g.nd,
-                                 g.maxnf, group_dft_due(b, g, s), (int)s, b->ntst, dm, st, fk);
+      const int r = enqueue_step(dt, g.nt, g.part, g.pgrid, g.nflux, b->tile_x, b->block, b->max_blocks, b->ddft + g.d0, g.nd,
+                                 g.maxnf, group_dft_due(b, g, s, captured), (int)s, b->ntst, dm, st, fk);
       if (r) return r;
     }
   }
@@ -2255,44 +2306,24 @@ static int batch_step(fdtd_batch* b, int64_t n, hipStream_t st) {
   if (int r = batch_static_owner(b)) return r;
   for (fdtd_plan* p : b->plans)
     if (p->step + n > p->max_steps) return fail(FDTD_ESTATE, "a member would exceed its max_steps");
-  const int64_t K = b->graph_steps;
-  int64_t done = 0;
-  if (K > 0) {
-    while (n - done >= K) {
-      std::vector<int64_t> key{K};
-      for (fdtd_plan* p : b->plans) key.push_back(plan_phase_key(p, p->step));
-      auto it = b->graphs.find(key);
-      if (it == b->graphs.end()) {
-        if (!b->cap) HIPCHK(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking));
-        Fork* fk = nullptr;
-        if (b->parallel) {
-          if (!b->fork) b->fork.reset(new Fork());
-          if (int rf = b->fork->init()) return rf;
-          fk = b->fork.get();
-        }
-        GraphEntry ge;
-        HIPCHK(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
-        const int r = batch_enqueue(b, K, b->cap, fk);
-        hipGraph_t gr = nullptr;
-        const hipError_t e = hipStreamEndCapture(b->cap, &gr);
-        if (r) {
-          if (gr) (void)hipGraphDestroy(gr);
-          return r;
-        }
-        if (e != hipSuccess) return fail(FDTD_EHIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
-        ge.graph = gr;
-        HIPCHK(hipGraphInstantiate(&ge.exec, gr, nullptr, nullptr, 0));
-        it = b->graphs.emplace(key, ge).first;
-      }
-      HIPCHK(hipGraphLaunch(it->second.exec, st));
-      for (fdtd_plan* p : b->plans) p->step += K;
-      done += K;
-    }
+  // as plan_step; a run ends with the first DFT launch of any member
+  if (n > 0 && caller_captures(st)) {
+    if (int r = batch_enqueue(b, n, st, nullptr, true)) return r;
+    for (fdtd_plan* p : b->plans) p->step += n;
+    return FDTD_OK;
   }
-  if (n - done > 0) {
-    const int r = batch_enqueue(b, n - done, st, nullptr);
-    if (r) return r;
-    for (fdtd_plan* p : b->plans) p->step += n - done;
+  auto enqueue = [&](int64_t k, hipStream_t on, Fork* fk) { return batch_enqueue(b, k, on, fk); };
+  for (int64_t done = 0; done < n;) {
+    int64_t k = n - done;
+    for (const fdtd_plan* p : b->plans) k = std::min(k, next_flush(p, p->step) - p->step);
+    bool graphed = false;
+    if (int r = b->graphs.launch(b->graph_steps, b->parallel, &k, st, enqueue, &graphed)) return r;
+    if (!graphed) {
+      k = std::min(n - done, k + 1);
+      if (int r = batch_enqueue(b, k, st, nullptr)) return r;
+    }
+    for (fdtd_plan* p : b->plans) p->step += k;
+    done += k;
   }
   return FDTD_OK;
 }
@@ -2341,10 +2372,10 @@ int fdtd_batch_time_kernels(fdtd_batch* b, int64_t n, void* stream, double* ms, 
       hipEvent_t a, z;
       if (int r = pair(c, &a, &z)) { cleanup(); return r; }
       const hipError_t e = fd_launch_step(c, b->dtiles[c] + g.t0[c], nt, b->tile_x, b->block, grid, (int)s, pc,
-                                          b->ntst, st, a, z);
+                                          b->ntst, g.nflux[c], st, a, z);
       if (e != hipSuccess) { cleanup(); return fail(FDTD_EHIP, "batch_time_kernels: %s", hipGetErrorString(e)); }
     }
-    if (group_dft_due(b, g, s) && g.nd > 0) {
+    if (group_dft_due(b, g, s, false) && g.nd > 0) {
       hipEvent_t a, z;
       if (int r = pair(FD_KERNEL_DFT, &a, &z)) { cleanup(); return r; }
       const hipError_t e = fd_launch_dft(b->ddft + g.d0, g.nd, (int)s, st, a, z);

@@ -76,8 +76,9 @@ struct fd_desc {
   // (cells without gain keep the arena's zeros)
   const uint32_t* glist;
   const uint32_t* elist;  // the (padded) cells with an edge that a gain cell shares, in blocks of rows
-  // o / plane and r / px of any cell index below 2^31 as (o m) >> s: {m, s}
-  uint32_t div_plane[2], div_px[2];
+  // o / plane and r / px of any cell index, n / flux_decim and n / ke of any step
+  // below 2^31 as (o m) >> s: {m, s}
+  uint32_t div_plane[2], div_px[2], div_decim[FD_MAXFLUX][2], div_ke[2];
   float* dmq[2];
   int ngain;
   int tile_x;  // xy tile width of the plan's step tiles (the T(t) partial slots)
@@ -133,6 +134,7 @@ struct fd_tile {
 // the shorter ones in all others.
 #define FD_TILE_ENERGY 2
 #define FD_TILE_NOENERGY 4
+#define FD_TILE_KE 8  // the plan records the energy in some steps
 
 // DFT work unit: FD_DFT_PTS plane points x 4 components x FD_DFT_QB frequencies.
 struct fd_dft_tile {
@@ -176,11 +178,19 @@ struct fd_xcd {
 // part == nullptr: grid-stride loop over the tiles with the plain XCD renumbering
 // start / stop (optional): events that take the kernel's own begin and end timestamps
 // nt: non-temporal field stores (the launch's working set exceeds the Infinity Cache)
+// nflux: the most flux planes (bits of fmask) any of the tiles has
 // Gain classes run the Lorentz medium; density-matrix plans step with the
 // classes without gain and add the fd_launch_dm passes.
 hipError_t fd_launch_step(int cls, const fd_tile* tiles, int ntiles, int tile_x, int block, int grid,
-                          int s, const fd_xcd* part, int nt, hipStream_t st, hipEvent_t start = nullptr,
+                          int s, const fd_xcd* part, int nt, int nflux, hipStream_t st, hipEvent_t start = nullptr,
                           hipEvent_t stop = nullptr);
+// ... by tile width (step.hip, compiled for each); checked and called by fd_launch_step
+hipError_t fd_launch_step_16(int cls, const fd_tile* tiles, int ntiles, int block, int grid, int s, const fd_xcd& part,
+                             int use, int nt, unsigned lds, hipStream_t st, hipEvent_t start, hipEvent_t stop);
+hipError_t fd_launch_step_32(int cls, const fd_tile* tiles, int ntiles, int block, int grid, int s, const fd_xcd& part,
+                             int use, int nt, unsigned lds, hipStream_t st, hipEvent_t start, hipEvent_t stop);
+hipError_t fd_launch_step_64(int cls, const fd_tile* tiles, int ntiles, int block, int grid, int s, const fd_xcd& part,
+                             int use, int nt, unsigned lds, hipStream_t st, hipEvent_t start, hipEvent_t stop);
 hipError_t fd_launch_dft(const fd_dft_tile* tiles, int ntiles, int s, hipStream_t st, hipEvent_t start = nullptr,
                          hipEvent_t stop = nullptr);
 hipError_t fd_launch_dft_preview(const fd_dft_tile* tiles, int ntiles, int flux, long long first, int count,
