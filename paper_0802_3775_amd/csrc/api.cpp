@@ -240,7 +240,8 @@ struct fdtd_plan {
   int nblk = 0, ntiles = 0;
   TileSet ts;   // the tuning's tiles: what a batch steps
   TileSet own;  // what the plan steps alone (own_zchunk)
-  int ntst = 0;  // non-temporal field stores: state beyond the Infinity Cache
+  bool beyond = false;  // step state beyond the Infinity Cache
+  int ntst = 0;  // non-temporal field stores
   std::vector<fd_dft_tile> dft;
   fd_dft_tile* ddft = nullptr;
   int maxnf = 0;
@@ -264,6 +265,7 @@ struct BGroup {
   fd_xcd part[FD_NCLASS] = {};
   int pgrid[FD_NCLASS] = {};
   int nflux[FD_NCLASS] = {};
+  bool beyond = false;  // the members' step state together exceeds the Infinity Cache
   int d0 = 0, nd = 0;
   int u0[3] = {}, nu[3] = {};
   int maxnf = 0;
@@ -536,15 +538,15 @@ size_t step_state_bytes(const fdtd_plan* p) {
   return b;
 }
 
-// Field stores go out non-temporal when the state of a step (the gain arrays by
-// the cells that have them) exceeds the Infinity Cache: the next step finds
+// Whether the state of a step (the gain arrays by the cells that have them)
+// exceeds the Infinity Cache.  Field stores then go out non-temporal: the next step finds
 // little of it there, and ordinary stores only displace what is still to be read.
 // Microseconds per step, ordinary against non-temporal, by state: Lorentz boxes
 // 195 MiB 89.3 / 99.6, 241 MiB 108.0 / 108.7, 485 MiB 156.6 / 150.5;
 // density-matrix boxes 229 MiB 158.7 / 162.6, 286 MiB 193.9 / 190.1, 457 MiB
 // 324.5 / 315.6; z-CPML slabs 255 MiB 78.6 / 73.6, 331 MiB 85.9 / 82.9; the
 // 200^3 box with CPML on all faces (440 MiB) 153.7 / 141.9.
-bool stores_nontemporal(const fdtd_plan* p) {
+bool beyond_cache(const fdtd_plan* p) {
   size_t b = (size_t)p->ncell * 49;
   for (int w = 0; w < 3; ++w) b += 6 * 4 * psi_elems(p, w);
   if (p->gm == 1) b += (size_t)p->ncell * 4 + (size_t)p->hdesc.ngain * 48;
@@ -825,12 +827,17 @@ struct DmLaunch {
   int n[3] = {0, 0, 0};
 };
 
+int step_rev(bool beyond, bool dm, int64_t s) { return beyond && !dm ? (int)(s & 1) : 0; }
+
 int enqueue_step(fd_tile* const dtiles[FD_NCLASS], const int* ntiles, const fd_xcd* part,
-                 const int* pgrid, const int* nflux, int tile_x, int block, int max_blocks, const fd_dft_tile* ddft, int ndft,
+                 const int* pgrid, const int* nflux, bool beyond, int tile_x, int block, int max_blocks, const fd_dft_tile* ddft, int ndft,
                  int maxnf, bool dft_due, int s, int ntst, const DmLaunch& dm, hipStream_t st, Fork* fk) {
   int used[FD_NCLASS], nused = 0;
   for (int c = 0; c < FD_NCLASS; ++c)
     if (ntiles[c] > 0) used[nused++] = c;
+  // beyond the Infinity Cache every other step goes down through the grid; with
+  // density-matrix passes the step always goes up, after the edge pass that went down
+  const int rev = step_rev(beyond, dm.n[0] > 0, s);
   const bool par = fk && nused > 1;
   if (par) HIPCHK(hipEventRecord(fk->fork, st));
   for (int u = 0; u < nused; ++u) {
@@ -843,7 +850,7 @@ int enqueue_step(fd_tile* const dtiles[FD_NCLASS], const int* ntiles, const fd_x
       on = fk->side[c];
       HIPCHK(hipStreamWaitEvent(on, fk->fork, 0));
     }
-    HIPCHK(fd_launch_step(c, dtiles[c], nt, tile_x, block, grid, s, pc, ntst, nflux[c], on));
+    HIPCHK(fd_launch_step(c, dtiles[c], nt, tile_x, block, grid, s, pc, ntst, nflux[c], rev, on));
     if (par && u > 0) HIPCHK(hipEventRecord(fk->join[c], on));
   }
   if (par)
@@ -897,7 +904,7 @@ int plan_enqueue(fdtd_plan* p, int64_t n, hipStream_t st, Fork* fk, bool capture
   int nt[FD_NCLASS];
   for (int c = 0; c < FD_NCLASS; ++c) nt[c] = (int)p->own.tiles[c].size();
   for (int64_t s = 0; s < n; ++s) {
-    const int r = enqueue_step(p->own.dev, nt, p->own.part, p->own.pgrid, p->own.nflux, p->tune.tile_x, p->tune.block,
+    const int r = enqueue_step(p->own.dev, nt, p->own.part, p->own.pgrid, p->own.nflux, p->beyond, p->tune.tile_x, p->tune.block,
                                p->tune.max_blocks, p->ddft, (int)p->dft.size(), p->maxnf,
                                plan_dft_due(p, p->step + s, captured), (int)s, p->ntst, plan_dm(p), st, fk);
     if (r) return r;
@@ -1556,9 +1563,10 @@ int fdtd_bind_arena(fdtd_plan* p, void* dev, size_t bytes, int64_t max_steps, vo
   if (int r = build_dm_units(p)) return r;
   HIPCHK(hipStreamSynchronize(st));
   p->step = 0;
+  p->beyond = beyond_cache(p);
   p->ntst = p->tune.stores == FDTD_STORES_NONTEMPORAL ? 1
             : p->tune.stores == FDTD_STORES_ORDINARY ? 0
-            : (stores_nontemporal(p) ? 1 : 0);
+            : (p->beyond ? 1 : 0);
   p->bound = true;
   return FDTD_OK;
 }
@@ -1889,7 +1897,7 @@ int fdtd_time_kernels(fdtd_plan* p, int64_t n, void* stream, double* ms, int64_t
       const fd_xcd* pc = p->tune.max_blocks > 0 ? nullptr : &p->own.part[c];
       const int r = record(c, [&](hipEvent_t a, hipEvent_t b) {
         return fd_launch_step(c, p->own.dev[c], nt, p->tune.tile_x, p->tune.block, grid, (int)s, pc, p->ntst,
-                              p->own.nflux[c], st, a,
+                              p->own.nflux[c], step_rev(p->beyond, !p->dmu[0].empty(), s), st, a,
                               b);
       });
       if (r) { cleanup(); return r; }
@@ -2094,6 +2102,7 @@ void batch_layout(fdtd_batch* b, fdtd_plan* const* plans, int32_t n, int gm) {
     g.m1 = m + 1;
     g.maxnf = std::max(g.maxnf, p->maxnf);
     held += bytes;
+    g.beyond = held > kInfinityCacheBytes;
     for (int c = 0; c < FD_NCLASS; ++c) {
       b->tiles[c].insert(b->tiles[c].end(), p->ts.tiles[c].begin(), p->ts.tiles[c].end());
       gcost[c].insert(gcost[c].end(), p->ts.cost[c].begin(), p->ts.cost[c].end());
@@ -2292,7 +2301,7 @@ static int batch_enqueue(fdtd_batch* b, int64_t n, hipStream_t st, Fork* fk, boo
     for (int c = 0; c < FD_NCLASS; ++c) dt[c] = b->dtiles[c] + g.t0[c];
     const DmLaunch dm = group_dm(b, g);
     for (int64_t s = 0; s < n; ++s) {
-      const int r = enqueue_step(dt, g.nt, g.part, g.pgrid, g.nflux, b->tile_x, b->block, b->max_blocks, b->ddft + g.d0, g.nd,
+      const int r = enqueue_step(dt, g.nt, g.part, g.pgrid, g.nflux, g.beyond, b->tile_x, b->block, b->max_blocks, b->ddft + g.d0, g.nd,
                                  g.maxnf, group_dft_due(b, g, s, captured), (int)s, b->ntst, dm, st, fk);
       if (r) return r;
     }
@@ -2372,7 +2381,7 @@ int fdtd_batch_time_kernels(fdtd_batch* b, int64_t n, void* stream, double* ms, 
       hipEvent_t a, z;
       if (int r = pair(c, &a, &z)) { cleanup(); return r; }
       const hipError_t e = fd_launch_step(c, b->dtiles[c] + g.t0[c], nt, b->tile_x, b->block, grid, (int)s, pc,
-                                          b->ntst, g.nflux[c], st, a, z);
+                                          b->ntst, g.nflux[c], step_rev(g.beyond, g.nu[0] > 0, s), st, a, z);
       if (e != hipSuccess) { cleanup(); return fail(FDTD_EHIP, "batch_time_kernels: %s", hipGetErrorString(e)); }
     }
     if (group_dft_due(b, g, s, false) && g.nd > 0) {

@@ -179,10 +179,11 @@ struct fd_xcd {
 // start / stop (optional): events that take the kernel's own begin and end timestamps
 // nt: non-temporal field stores (the launch's working set exceeds the Infinity Cache)
 // nflux: the most flux planes (bits of fmask) any of the tiles has
+// rev: each XCD's part from its end
 // Gain classes run the Lorentz medium; density-matrix plans step with the
 // classes without gain and add the fd_launch_dm passes.
 hipError_t fd_launch_step(int cls, const fd_tile* tiles, int ntiles, int tile_x, int block, int grid,
-                          int s, const fd_xcd* part, int nt, int nflux, hipStream_t st, hipEvent_t start = nullptr,
+                          int s, const fd_xcd* part, int nt, int nflux, int rev, hipStream_t st, hipEvent_t start = nullptr,
                           hipEvent_t stop = nullptr);
 // ... by tile width (step.hip, compiled for each); checked and called by fd_launch_step
 hipError_t fd_launch_step_16(int cls, const fd_tile* tiles, int ntiles, int block, int grid, int s, const fd_xcd& part,

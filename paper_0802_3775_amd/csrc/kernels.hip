@@ -470,10 +470,17 @@ __device__ __forceinline__ void dm_stage_mats(const cdesc* d, DmMats& sm, F&& lo
 // kDmRun consecutive units are kept on one XCD, so that the fields and increments
 // a unit gathers from the rows and planes beside its own cells are in that XCD's
 // L2 from the units next to it (gain cells are numbered in blocks of 8 x 8 rows).
+// REV: from the last unit to the first.  The step kernel goes up through the grid,
+// the predictor down, the corrector up and the edge pass down, so that each starts
+// with what the one before it has just read and written and the Infinity Cache
+// still holds: 168^3 box 301.6 -> 287.7 us per step (predictor 61.6 -> 58, corrector
+// 112 -> 103), the paper's 200^3 lasing box 301 -> 298.
 constexpr int kDmRun = 32;
+template <bool REV>
 __device__ __forceinline__ int dm_unit(int w, int n) {
-  if (w >= n / (8 * kDmRun) * (8 * kDmRun)) return w;  // the rest, in order
-  const int x = w % 8, q = w / 8;
+  const int full = n / (8 * kDmRun) * (8 * kDmRun);
+  if (w >= full) return w;  // the rest, in order
+  const int x = w % 8, q = REV ? full / 8 - 1 - w / 8 : w / 8;  // a unit is on the same XCD in every pass
   return (q / kDmRun * 8 + x) * kDmRun + q % kDmRun;
 }
 
@@ -608,7 +615,7 @@ __device__ __forceinline__ void dm_centre_pred(const cdesc* d, const Nbr& b, uin
 
 __global__ __launch_bounds__(FD_DM_CELLS) void dm_predict_kernel(const fd_dm_unit* __restrict__ units, int s) {
   __shared__ DmMats sm;
-  const fd_dm_unit u = units[dm_unit((int)blockIdx.x, (int)gridDim.x)];
+  const fd_dm_unit u = units[dm_unit<true>((int)blockIdx.x, (int)gridDim.x)];
   const cdesc* d = (const cdesc*)u.d;
   const long long n = d->step + s;
   const int par = (int)(n & 1), t = (int)threadIdx.x;
@@ -669,7 +676,7 @@ __device__ __forceinline__ void dm_centre_corr(const cdesc* d, const DmMats& sm,
 
 __global__ __launch_bounds__(FD_DM_CELLS) void dm_correct_kernel(const fd_dm_unit* __restrict__ units, int s) {
   __shared__ DmMats sm;
-  const fd_dm_unit u = units[dm_unit((int)blockIdx.x, (int)gridDim.x)];
+  const fd_dm_unit u = units[dm_unit<false>((int)blockIdx.x, (int)gridDim.x)];
   const cdesc* d = (const cdesc*)u.d;
   const long long n = d->step + s;
   const int par = (int)(n & 1), t = (int)threadIdx.x;
@@ -727,7 +734,7 @@ __device__ __forceinline__ void dm_edge_sums(const cdesc* d, const Nbr& b, uint3
 
 __global__ __launch_bounds__(FD_DM_EDGES) void dm_edges_kernel(const fd_dm_unit* __restrict__ units, int s) {
   __shared__ DmMats sm;
-  const fd_dm_unit u = units[dm_unit((int)blockIdx.x, (int)gridDim.x)];
+  const fd_dm_unit u = units[dm_unit<true>((int)blockIdx.x, (int)gridDim.x)];
   const cdesc* d = (const cdesc*)u.d;
   const int t = (int)threadIdx.x;
   const long long n = d->step + s;
@@ -795,7 +802,8 @@ __global__ __launch_bounds__(FD_MAXBLOCK) void dm_diag_kernel(const fd_dm_unit* 
 }  // namespace
 
 hipError_t fd_launch_step(int cls, const fd_tile* tiles, int ntiles, int tile_x, int block, int grid, int s,
-                          const fd_xcd* part, int nt, int nflux, hipStream_t st, hipEvent_t start, hipEvent_t stop) {
+                          const fd_xcd* part, int nt, int nflux, int rev, hipStream_t st, hipEvent_t start,
+                          hipEvent_t stop) {
   if (ntiles <= 0) return hipSuccess;
   if (nflux < 0 || nflux > FD_MAXFLUX) return hipErrorInvalidValue;
   const unsigned lds = (unsigned)(nflux * 4 * FD_MAXBLOCK * (int)sizeof(float));
@@ -815,6 +823,7 @@ hipError_t fd_launch_step(int cls, const fd_tile* tiles, int ntiles, int tile_x,
     if (grid < 8 * longest) return hipErrorInvalidValue;
     pz = *part;
     use = 1;
+    use |= rev ? 2 : 0;
   }
   switch (tile_x) {
     case 16: return fd_launch_step_16(cls, tiles, ntiles, block, grid, s, pz, use, nt, lds, st, start, stop);
