@@ -795,11 +795,11 @@ int build_dm_units(fdtd_plan* p) {
     }
     p->dm_cells[0] = p->dm_cells[1] = ng;
     p->dm_cells[2] = ne;
-    // predictor: state 72 + E^n and A of the cell's edges 24 + map and list 5
+    // predictor: state 60 + E^n and A of the cell's edges 24 + map and list 5
     // + Q* 12; corrector: state 72 + 72, fields 24, neighbours' Q* 12, Q 12,
     // map and list 5; edges, per listed cell: its entry 4, the sharers' Q 12,
     // A in and E out 24, its map 1
-    p->dm_bytes[0] = 113.0 * ng;
+    p->dm_bytes[0] = 101.0 * ng;
     p->dm_bytes[1] = 197.0 * ng;
     p->dm_bytes[2] = 41.0 * (double)ne;
   }
@@ -1186,8 +1186,10 @@ int fdtd_bind_arena(fdtd_plan* p, void* dev, size_t bytes, int64_t max_steps, vo
       p->has_gain = true;
       for (int l = 0; l < 4; ++l) {
         const float hi = (float)p->mats[q].n_init[l];
-        ninit[8 * q + l] = hi;
-        ninit[8 * q + 4 + l] = (float)(p->mats[q].n_init[l] - (double)hi);
+        const float lo = (float)(p->mats[q].n_init[l] - (double)hi);
+        const float sum = hi + lo;  // the high part, also where lo was rounded up to half its last place
+        ninit[8 * q + l] = sum;
+        ninit[8 * q + 4 + l] = (float)((double)hi + (double)lo - (double)sum);
       }
     }
   }

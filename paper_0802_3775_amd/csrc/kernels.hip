@@ -552,7 +552,10 @@ struct DmCell {
 };
 
 // The cell and state of gain ordinal g (issued before the material table is
-// waited for), then what needs the table.
+// waited for), then what needs the table.  LO: with the populations' low parts.
+// The predictor leaves them out (12 of 113 bytes): a pair is stored with hi the
+// rounded sum of both (two_sum, and n_init at bind), so hi is the population.
+template <bool LO>
 __device__ __forceinline__ void dm_load_state(const cdesc* d, uint32_t g, DmCell& z) {
   const size_t ncs = (size_t)d->ncell;
   const gf* pop = G((const float*)d->pop);
@@ -562,7 +565,7 @@ __device__ __forceinline__ void dm_load_state(const cdesc* d, uint32_t g, DmCell
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
     z.nh[q] = state(q);
-    z.nl[q] = state(3 + q);
+    z.nl[q] = LO ? state(3 + q) : 0.0f;
     z.c[q] = {state(6 + q), state(9 + q)};
     z.x[q] = {state(12 + q), state(15 + q)};
   }
@@ -620,7 +623,7 @@ __global__ __launch_bounds__(FD_DM_CELLS) void dm_predict_kernel(const fd_dm_uni
   const long long n = d->step + s;
   const int par = (int)(n & 1), t = (int)threadIdx.x;
   DmCell z;
-  dm_stage_mats(d, sm, [&] { dm_load_state(d, (uint32_t)(u.first + (t < u.count ? t : 0)), z); });
+  dm_stage_mats(d, sm, [&] { dm_load_state<false>(d, (uint32_t)(u.first + (t < u.count ? t : 0)), z); });
   if (t >= u.count) return;
   dm_load_medium(d, sm, n, z);
   const Nbr b = neighbours(d, z.p);
@@ -681,7 +684,7 @@ __global__ __launch_bounds__(FD_DM_CELLS) void dm_correct_kernel(const fd_dm_uni
   const long long n = d->step + s;
   const int par = (int)(n & 1), t = (int)threadIdx.x;
   DmCell z;
-  dm_stage_mats(d, sm, [&] { dm_load_state(d, (uint32_t)(u.first + (t < u.count ? t : 0)), z); });
+  dm_stage_mats(d, sm, [&] { dm_load_state<true>(d, (uint32_t)(u.first + (t < u.count ? t : 0)), z); });
   if (t >= u.count) return;
   dm_load_medium(d, sm, n, z);
   const Nbr b = neighbours(d, z.p);
