@@ -134,6 +134,7 @@ struct fd_tile {
 // the shorter ones in all others.
 #define FD_TILE_ENERGY 2
 #define FD_TILE_NOENERGY 4
+#define FD_TILE_XYSLAB 16  // some cell or halo cell of the tile lies in an x or y CPML slab
 #define FD_TILE_KE 8  // the plan records the energy in some steps
 
 // DFT work unit: FD_DFT_PTS plane points x 4 components x FD_DFT_QB frequencies.

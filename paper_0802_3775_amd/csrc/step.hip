@@ -938,17 +938,19 @@ __device__ __forceinline__ int xcd_tile(int w, int n) {
 // With a cost-balanced partition (use_part), workgroup w takes tile
 // part.start[x] + w/8 of XCD x = w mod 8, or nothing if that part is shorter; with
 // bit 1 of use_part set, each part from its end.  Steps of grids beyond the
-// Infinity Cache alternate: a step then starts with the tiles whose fields the step before wrote last and the Infinity
-// Cache still holds (200x200x200 slab with ordinary stores 128 -> 115 us,
+// Infinity Cache alternate: a step then starts with the tiles whose fields the
+// step before wrote last and the Infinity Cache still holds (200x200x200 slab with ordinary stores 128 -> 115 us,
 // 176x176x176 78.6 -> 74.8; with non-temporal ones 110.0 -> 109.4 and 72.6 ->
 // 72.3; in the cache 16 batched realizations took 228.4 -> 229.8).
-// otherwise the workgroups loop over the renumbered tile list.
+// Without a partition the workgroups loop over the renumbered tile list.
 template <int TX, int PM, int GAIN, bool NT>
 __device__ __forceinline__ void step_body(const fd_tile* __restrict__ tiles, int ntiles, int s, const fd_xcd& part,
                                           int use_part, Lds<TX>& lds) {
   // A march without the code of sources, probes, flux planes and energy for the
-  // tiles that have none; and z-only CPML launches specialise their interior tiles
-  // (the all-axes kernel keeps one general march).
+  // tiles that have none; z-only CPML launches specialise their interior tiles, and
+  // all-axes launches without gain their lean tiles off the x and y slabs, which lose
+  // the psi registers and tests of those axes (a folded or merged launch holds them:
+  // 200x200x200 box 139.5 -> 138.0 us).
   auto run = [&](const fd_tile& tl) {
     // (the look at the step only in plans that record the energy: it is a round trip
     // before the tile's first loads)
@@ -965,6 +967,13 @@ __device__ __forceinline__ void step_body(const fd_tile* __restrict__ tiles, int
       if (!(tl.flags & FD_TILE_ZSLAB)) {
         if (sp) run_tile<TX, PM, GAIN, false, NT, true>(tl, s, lds);
         else run_tile<TX, PM, GAIN, false, NT, false>(tl, s, lds);
+        return;
+      }
+    }
+    if constexpr (PM == 7 && GAIN == 0) {
+      if (!sp && !(tl.flags & FD_TILE_XYSLAB)) {
+        if (tl.flags & FD_TILE_ZSLAB) run_tile<TX, 4, GAIN, true, NT, false>(tl, s, lds);
+        else run_tile<TX, 4, GAIN, false, NT, false>(tl, s, lds);
         return;
       }
     }
