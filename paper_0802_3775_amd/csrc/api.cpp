@@ -510,10 +510,10 @@ int pml_t(const fdtd_plan* p, int w) {
 }
 size_t psi_elems(const fdtd_plan* p, int w) {
   const size_t t = (size_t)pml_t(p, w);
-  const size_t nx = p->g.nx, ny = p->g.ny, nz = p->g.nz;
+  const size_t ny = p->g.ny, nz = p->g.nz;
   if (w == 2) return t * (size_t)p->px * ny;  // z slabs are whole (padded) planes
-  if (w == 0) return nz * ny * t;
-  return nz * t * nx;
+  if (w == 0) return nz * ny * t;  // the low slab, then the high one
+  return nz * t * (size_t)p->px;
 }
 
 int gain_model_of(const std::vector<fdtd_material>& mats) {

@@ -86,11 +86,17 @@ __device__ __forceinline__ int slab(const Ctx& x, int w, int p) {
   return -1;
 }
 
-// psi array offset for axis w, slab index sp, at (i, j, k)
+// psi array offset for axis w, slab index sp, at (i, j, k).  z slabs are whole
+// planes.  The rows of y slabs have the fields' pitch, and each x slab is an array of
+// its own: a tile's rows of one x slab follow each other, where rows that held both
+// slabs left most 128-byte lines to two tiles at the grid's two ends (200x200x200
+// box 138.1 -> 135.5 us; while interior tiles took the all-axes march too, 139.9 and
+// 140.3).
 __device__ __forceinline__ int psi_off(const Ctx& x, int w, int sp, int i, int j, int k) {
   if (w == 2) return sp * x.plane + j * x.rx + i;
-  if (w == 0) return (k * x.ny + j) * x.t[0] + sp;
-  return (k * x.t[1] + sp) * x.nx + i;
+  if (w == 1) return (k * x.t[1] + sp) * x.rx + i;
+  const bool up = sp >= x.lo[0];
+  return (k * x.ny + j) * (up ? x.hi[0] : x.lo[0]) + (up ? x.lo[0] * x.ny * x.nz + sp - x.lo[0] : sp);
 }
 
 // CPML stretch of one difference d along axis w at index p (E position when
@@ -530,11 +536,11 @@ __device__ __forceinline__ void run_tile(const fd_tile& tl, int s_rel, Lds<TX>& 
     float aH[6] = {}, aE[6] = {}, aHh[4] = {}, gzE[3] = {}, gzH[3] = {};
     uint32_t ox = 0, oy = 0, oz = 0, ohx = 0, ohy = 0, ohz = 0;
     if (AX) {
-      ox = (act && sxo >= 0) ? (uint32_t)((k * x.ny + j) * x.t[0] + sxo) : 0u;
-      oy = (act && syo >= 0) ? (uint32_t)((k * x.t[1] + syo) * x.nx + i) : 0u;
+      ox = (act && sxo >= 0) ? (uint32_t)psi_off(x, 0, sxo, i, j, k) : 0u;
+      oy = (act && syo >= 0) ? (uint32_t)psi_off(x, 1, syo, i, j, k) : 0u;
       oz = (act && sz >= 0) ? (uint32_t)(sz * x.plane + c) : 0u;
-      ohx = (hact && sxh >= 0) ? (uint32_t)((k * x.ny + hgj) * x.t[0] + sxh) : 0u;
-      ohy = (hact && syh >= 0) ? (uint32_t)((k * x.t[1] + syh) * x.nx + hgi) : 0u;
+      ohx = (hact && sxh >= 0) ? (uint32_t)psi_off(x, 0, sxh, hgi, hgj, k) : 0u;
+      ohy = (hact && syh >= 0) ? (uint32_t)psi_off(x, 1, syh, hgi, hgj, k) : 0u;
       ohz = (hact && sz >= 0) ? (uint32_t)(sz * x.plane + h_off) : 0u;
       // own H: Hx(y, z), Hy(z, x), Hz(x, y); own E in the same order.  The
       // reads of an axis whose slabs neither the tile (x, y) nor the plane (z)
@@ -950,7 +956,7 @@ __device__ __forceinline__ void step_body(const fd_tile* __restrict__ tiles, int
   // tiles that have none; z-only CPML launches specialise their interior tiles, and
   // all-axes launches without gain their lean tiles off the x and y slabs, which lose
   // the psi registers and tests of those axes (a folded or merged launch holds them:
-  // 200x200x200 box 139.5 -> 138.0 us).
+  // 200x200x200 box 139.5 -> 138.0 us, with the x slabs apart 139.9 -> 135.4).
   auto run = [&](const fd_tile& tl) {
     // (the look at the step only in plans that record the energy: it is a round trip
     // before the tile's first loads)
