@@ -354,12 +354,12 @@ int fdtd_class_cells(const fdtd_plan* p, int64_t* cells /* FDTD_NKERNEL */);
    Lorentz gain cell (P^n, P^{n-1}, populations in; P^{n+1}, populations out);
    the DFT entry, a launch that adds a full ring of 32 samples: the 4 complex FP64
    accumulators read + written per plane point and frequency plus the ring read
-   (the samples are stored by the step kernels, 16 bytes per point); per density-matrix gain
-   cell 101 (predictor: 15 state floats, the cell's share of E^n and A, map and
-   list, Q*) and 197 (corrector: the state
-   read and written, fields, neighbours' Q*, Q), 41 per cell whose edges a gain
-   cell shares (its list entry, the sharers' Q, A in, E out, map), 32 per
-   flux-plane point for the diagnostics. */
+   (the samples are stored by the step kernels, 16 bytes per point); per
+   density-matrix gain cell 101 (predictor: 15 state floats, the cell's share of
+   E^n and A, map and list, Q*) and 197 (corrector: the state read and written,
+   fields, neighbours' Q*, Q), 41 per cell whose edges a gain cell shares (its list
+   entry, the sharers' Q, A in, E out, map), 32 per flux-plane point for the
+   diagnostics. */
 int fdtd_class_bytes(const fdtd_plan* p, double* bytes /* FDTD_NKERNEL */);
 /* Advance n steps without graphs, launching every kernel with a pair of hipEvents
    bound to the launch (hipExtLaunchKernelGGL start/stop: the kernel's own begin

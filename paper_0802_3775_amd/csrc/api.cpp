@@ -508,12 +508,14 @@ hipError_t copy_rows_to_host(const fdtd_plan* p, void* host, const void* dev, si
 int pml_t(const fdtd_plan* p, int w) {
   return p->g.bc[w] == FDTD_BC_PEC ? p->g.pml_lo[w] + p->g.pml_hi[w] : 0;
 }
-size_t psi_elems(const fdtd_plan* p, int w) {
+// Elements of one psi array of axis w, as laid out; touched: without the row padding
+// of the y slabs, which a step neither reads nor writes.
+size_t psi_elems(const fdtd_plan* p, int w, bool touched = false) {
   const size_t t = (size_t)pml_t(p, w);
   const size_t ny = p->g.ny, nz = p->g.nz;
   if (w == 2) return t * (size_t)p->px * ny;  // z slabs are whole (padded) planes
   if (w == 0) return nz * ny * t;  // the low slab, then the high one
-  return nz * t * (size_t)p->px;
+  return nz * t * (size_t)(touched ? p->g.nx : p->px);
 }
 
 int gain_model_of(const std::vector<fdtd_material>& mats) {
@@ -533,13 +535,13 @@ constexpr size_t kInfinityCacheBytes = (size_t)256 << 20;
 size_t step_state_bytes(const fdtd_plan* p) {
   // (the cells a step touches: row padding is never read or written)
   size_t b = (size_t)p->ncell * 49;
-  for (int w = 0; w < 3; ++w) b += 6 * 4 * psi_elems(p, w);
+  for (int w = 0; w < 3; ++w) b += 6 * 4 * psi_elems(p, w, true);
   if (p->has_gain) b += (size_t)p->ncell * (p->gm == 2 ? 144 : 48);
   return b;
 }
 
-// Whether the state of a step (the gain arrays by the cells that have them)
-// exceeds the Infinity Cache.  Field stores then go out non-temporal: the next step finds
+// Whether the state of a step (the gain arrays by the cells that have them) exceeds
+// the Infinity Cache.  Field stores then go out non-temporal: the next step finds
 // little of it there, and ordinary stores only displace what is still to be read.
 // Microseconds per step, ordinary against non-temporal, by state: Lorentz boxes
 // 195 MiB 89.3 / 99.6, 241 MiB 108.0 / 108.7, 485 MiB 156.6 / 150.5;
@@ -548,7 +550,7 @@ size_t step_state_bytes(const fdtd_plan* p) {
 // 200^3 box with CPML on all faces (440 MiB) 153.7 / 141.9.
 bool beyond_cache(const fdtd_plan* p) {
   size_t b = (size_t)p->ncell * 49;
-  for (int w = 0; w < 3; ++w) b += 6 * 4 * psi_elems(p, w);
+  for (int w = 0; w < 3; ++w) b += 6 * 4 * psi_elems(p, w, true);
   if (p->gm == 1) b += (size_t)p->ncell * 4 + (size_t)p->hdesc.ngain * 48;
   if (p->gm == 2) b += (size_t)p->hdesc.ngain * 96;
   return b > kInfinityCacheBytes;

@@ -432,18 +432,18 @@ __global__ void init_pop_kernel(const uint8_t* __restrict__ map, const float* __
 //   corrector  E* = A - [Q*]/eps,  rho^{n+1} = S(rho^n; <(E^n + E*)/2>),
 //              Q = P(rho^{n+1}) - P(rho^n) + dt J
 //   edges      E^{n+1} = A - [Q]/eps
-// (The passes move their bytes at 4.2-4.7 TB/s, near the 5.1 TB/s of a large copy:
-// on the 168^3 box, 2.09 M gain cells, counted 291 MB in 61.6 us, 499 MB in 112 us
-// and 136 MB in 32 us.  Numbering the gain cells and edges in blocks of 8 x 8 rows
-// with neighbouring units on one XCD took the corrector's traffic from 636 MB, and
-// neighbour offsets without wall tests and divisions its instructions from 1,200 to
-// 930 a wave and its registers from 135 to 112, four waves per SIMD instead of
-// three: 124 -> 112 us.)
 // with S = R(dt/2) C(E) R(dt/2), P_c = 2 kappa Re rho_0c, J the
 // spontaneous-emission noise current at the centre and eps that of the edge's
 // own voxel.  Each pass reads what the previous one wrote for neighbouring
 // cells, so the passes are separate launches; a cell's rho is read and written
 // only by its own thread.
+// Memory bounds the passes: on the 168^3 box, 2.09 M gain cells, they count 266 MB in
+// 54 us, 499 MB in 105 us and 136 MB in 31 us, 4.4-4.9 TB/s beside the 5.1 TB/s of a
+// large copy.  Numbering the gain cells and edges in blocks of 8 x 8 rows with
+// neighbouring units on one XCD took the corrector's traffic from 636 MB to 499, and
+// neighbour offsets without wall tests and divisions its instructions from 1,200 to
+// 930 a wave and its registers from 135 to 112, four waves per SIMD instead of three:
+// 124 -> 112 us, the rest by the order of the passes (dm_unit).
 
 // The plan's material table in LDS (a gain cell's own medium, an edge's
 // permittivity), staged once per workgroup: a work unit's cells belong to one

@@ -945,9 +945,10 @@ __device__ __forceinline__ int xcd_tile(int w, int n) {
 // part.start[x] + w/8 of XCD x = w mod 8, or nothing if that part is shorter; with
 // bit 1 of use_part set, each part from its end.  Steps of grids beyond the
 // Infinity Cache alternate: a step then starts with the tiles whose fields the
-// step before wrote last and the Infinity Cache still holds (200x200x200 slab with ordinary stores 128 -> 115 us,
-// 176x176x176 78.6 -> 74.8; with non-temporal ones 110.0 -> 109.4 and 72.6 ->
-// 72.3; in the cache 16 batched realizations took 228.4 -> 229.8).
+// step before wrote last and the Infinity Cache still holds (200x200x200 slab with
+// ordinary stores 128 -> 115 us, 176x176x176 78.6 -> 74.8; with non-temporal ones
+// 110.0 -> 109.4 and 72.6 -> 72.3; in the cache 16 batched realizations took 228.4
+// -> 229.8).
 // Without a partition the workgroups loop over the renumbered tile list.
 template <int TX, int PM, int GAIN, bool NT>
 __device__ __forceinline__ void step_body(const fd_tile* __restrict__ tiles, int ntiles, int s, const fd_xcd& part,
@@ -1000,9 +1001,11 @@ __device__ __forceinline__ void step_body(const fd_tile* __restrict__ tiles, int
   }
 }
 
+// All-axes CPML with Lorentz gain: held at three waves per SIMD (168 VGPRs; two spill.
+// With 180, two waves, the 168^3 box took 191 us per step instead of 150).
 template <int TX, int PM, int GAIN, bool NT>
-__global__ __launch_bounds__(FD_MAXBLOCK) __attribute__((amdgpu_waves_per_eu(PM == 7 && GAIN ? 3 : 1))) void step_kernel(const fd_tile* __restrict__ tiles, int ntiles, int s,
-                                                           fd_xcd part, int use_part) {
+__global__ __launch_bounds__(FD_MAXBLOCK) __attribute__((amdgpu_waves_per_eu(PM == 7 && GAIN ? 3 : 1))) void step_kernel(
+    const fd_tile* __restrict__ tiles, int ntiles, int s, fd_xcd part, int use_part) {
   __shared__ Lds<TX> lds;
   step_body<TX, PM, GAIN, NT>(tiles, ntiles, s, part, use_part, lds);
 }
