@@ -958,7 +958,9 @@ __device__ __forceinline__ void step_body(const fd_tile* __restrict__ tiles, int
   // all-axes launches without gain their lean tiles off the x and y slabs, which lose
   // the psi registers and tests of those axes (a folded or merged launch holds them:
   // 200x200x200 box 139.5 -> 138.0 us, with the x slabs apart 139.9 -> 135.4).
-  auto run = [&](const fd_tile& tl) {
+  // Inlined by hand: as a call, which the compiler chose for the z-CPML class with
+  // gain, the marches took 264 VGPRs instead of 146 (160x160x160, 111 us and 84).
+  auto run = [&](const fd_tile& tl) __attribute__((always_inline)) {
     // (the look at the step only in plans that record the energy: it is a round trip
     // before the tile's first loads)
     bool edue = false;
