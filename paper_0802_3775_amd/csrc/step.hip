@@ -950,7 +950,15 @@ __device__ __forceinline__ int xcd_tile(int w, int n) {
 // 110.0 -> 109.4 and 72.6 -> 72.3; in the cache 16 batched realizations took 228.4
 // -> 229.8).
 // Without a partition the workgroups loop over the renumbered tile list.
-template <int TX, int PM, int GAIN, bool NT>
+// FORM: 0 the partition, 1 the loop, 2 either.  The plain and all-axes classes with
+// Lorentz gain have the loop in kernels of their own: what it keeps in registers cost
+// the partition's form 17 VGPRs (32 wide: plain 142 -> 125 and four waves per SIMD,
+// all-axes 168 -> 154; 128x128x96 with gain 36.2 -> 33.4 us per step, the 168^3 box
+// 150.9 -> 148.6).  The z-CPML class with gain lost 1% apart (160^3 84.3 -> 85.1), the
+// classes without gain nothing or up to 0.7%; one call of the march for both forms
+// made every class slower (the 200^3 box 135.5 -> 149.3 us).
+constexpr bool loop_apart(int pm, int gain) { return gain != 0 && pm != 4; }
+template <int TX, int PM, int GAIN, bool NT, int FORM>
 __device__ __forceinline__ void step_body(const fd_tile* __restrict__ tiles, int ntiles, int s, const fd_xcd& part,
                                           int use_part, Lds<TX>& lds) {
   // A march without the code of sources, probes, flux planes and energy for the
@@ -989,7 +997,7 @@ __device__ __forceinline__ void step_body(const fd_tile* __restrict__ tiles, int
     if (sp) run_tile<TX, PM, GAIN, (PM & 4) != 0, NT, true>(tl, s, lds);
     else run_tile<TX, PM, GAIN, (PM & 4) != 0, NT, false>(tl, s, lds);
   };
-  if (use_part) {
+  if (FORM == 0 || (FORM == 2 && use_part)) {
     const int x = (int)blockIdx.x % 8, q = (int)blockIdx.x / 8;
     if (q < part.count[x]) {
       const fd_tile tl = tiles[part.start[x] + (use_part & 2 ? part.count[x] - 1 - q : q)];
@@ -997,19 +1005,21 @@ __device__ __forceinline__ void step_body(const fd_tile* __restrict__ tiles, int
     }
     return;
   }
-  for (int w = blockIdx.x; w < ntiles; w += gridDim.x) {
-    const fd_tile tl = tiles[xcd_tile(w, ntiles)];
-    run(tl);
+  if constexpr (FORM != 0) {
+    for (int w = blockIdx.x; w < ntiles; w += gridDim.x) {
+      const fd_tile tl = tiles[xcd_tile(w, ntiles)];
+      run(tl);
+    }
   }
 }
 
-// All-axes CPML with Lorentz gain: held at three waves per SIMD (168 VGPRs; two spill.
-// With 180, two waves, the 168^3 box took 191 us per step instead of 150).
+// All-axes CPML with Lorentz gain: held at three waves per SIMD (154 VGPRs; with 180,
+// two waves, the 168^3 box took 191 us per step instead of 150).
 template <int TX, int PM, int GAIN, bool NT>
 __global__ __launch_bounds__(FD_MAXBLOCK) __attribute__((amdgpu_waves_per_eu(PM == 7 && GAIN ? 3 : 1))) void step_kernel(
     const fd_tile* __restrict__ tiles, int ntiles, int s, fd_xcd part, int use_part) {
   __shared__ Lds<TX> lds;
-  step_body<TX, PM, GAIN, NT>(tiles, ntiles, s, part, use_part, lds);
+  step_body<TX, PM, GAIN, NT, loop_apart(PM, GAIN) ? 0 : 2>(tiles, ntiles, s, part, use_part, lds);
 }
 
 // All-axes CPML without gain: capped at four waves per SIMD (128 VGPRs; the
@@ -1018,7 +1028,14 @@ template <int TX, bool NT>
 __global__ __launch_bounds__(FD_MAXBLOCK) __attribute__((amdgpu_waves_per_eu(4))) void step_kernel_ax(
     const fd_tile* __restrict__ tiles, int ntiles, int s, fd_xcd part, int use_part) {
   __shared__ Lds<TX> lds;
-  step_body<TX, 7, 0, NT>(tiles, ntiles, s, part, use_part, lds);
+  step_body<TX, 7, 0, NT, 2>(tiles, ntiles, s, part, use_part, lds);
+}
+
+template <int TX, int PM, bool NT>
+__global__ __launch_bounds__(FD_MAXBLOCK) __attribute__((amdgpu_waves_per_eu(3))) void step_kernel_gain_loop(
+    const fd_tile* __restrict__ tiles, int ntiles, int s, fd_xcd part) {
+  __shared__ Lds<TX> lds;
+  step_body<TX, PM, 1, NT, 1>(tiles, ntiles, s, part, 0, lds);
 }
 
 }  // namespace
@@ -1027,6 +1044,17 @@ __global__ __launch_bounds__(FD_MAXBLOCK) __attribute__((amdgpu_waves_per_eu(4))
 template <int TX, int PM, int GAIN>
 static void launch_one(const fd_tile* tiles, int ntiles, int block, int grid, int s, const fd_xcd& part, int use,
                        int nt, unsigned lds, hipStream_t st, hipEvent_t start, hipEvent_t stop) {
+  if constexpr (loop_apart(PM, GAIN)) {
+    if (!use) {
+      if (nt)
+        hipExtLaunchKernelGGL(step_kernel_gain_loop<TX, PM, true>, dim3(grid), dim3(block), lds, st, start, stop, 0,
+                              tiles, ntiles, s, part);
+      else
+        hipExtLaunchKernelGGL(step_kernel_gain_loop<TX, PM, false>, dim3(grid), dim3(block), lds, st, start, stop, 0,
+                              tiles, ntiles, s, part);
+      return;
+    }
+  }
   if constexpr (PM == 7 && GAIN == 0) {
     if (nt)
       hipExtLaunchKernelGGL(step_kernel_ax<TX, true>, dim3(grid), dim3(block), lds, st, start, stop, 0, tiles, ntiles,
