@@ -248,8 +248,10 @@ int fdtd_bind_arena(fdtd_plan* p, void* dev, size_t bytes, int64_t max_steps, vo
 
 /* Advance n leapfrog steps ("Sample and numerical approach": FDTD after
    Taflove, with the Maxwell-Bloch gain cells) on the stream, asynchronous;
-   FDTD_ESTATE past max_steps, leaving the state untouched.  Step count, cell
-   count and dt of the plan. */
+   FDTD_ESTATE past max_steps, leaving the state untouched.  Steps captured into
+   a graph of the caller's are counted when they are captured, not when they are
+   replayed; the graph runs them from whatever step the device is at.  Step count,
+   cell count and dt of the plan. */
 int fdtd_step(fdtd_plan* p, int64_t n, void* stream);
 int64_t fdtd_step_count(const fdtd_plan* p);
 int64_t fdtd_cell_count(const fdtd_plan* p);

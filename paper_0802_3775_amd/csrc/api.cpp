@@ -237,6 +237,7 @@ struct fdtd_plan {
   fd_desc hdesc{};
   fd_desc* ddesc = nullptr;
   int64_t step = 0;
+  bool captured = false;  // the caller has captured steps: the device may be at another step than the host counts
   int nblk = 0, ntiles = 0;
   TileSet ts;   // the tuning's tiles: what a batch steps
   TileSet own;  // what the plan steps alone (own_zchunk)
@@ -886,13 +887,13 @@ int64_t next_flush(const fdtd_plan* p, int64_t n) {
   return best;
 }
 
-// In a graph that the caller captures, a DFT launch follows every sampled step, as
-// the replays may come to a full ring at any of them (the kernel looks).
-bool plan_dft_due(const fdtd_plan* p, int64_t n, bool captured) {
-  if (!captured) return next_flush(p, n) == n;
-  for (const Flux& f : p->flux)
-    if (f.nf > 0 && n % f.decim == 0) return true;
-  return false;
+// Whether the DFT launch follows step n.  In a graph that the caller captures it
+// follows every step of a plan with spectra: replays may come to a full ring at any
+// offset of the graph, whatever its length (the kernel looks at the device's step).
+// So it does in later steps, as the host's count includes captured steps that are
+// yet to be replayed, or misses repeated replays.
+bool plan_dft_due(const fdtd_plan* p, int64_t n) {
+  return p->captured ? !p->dft.empty() : next_flush(p, n) == n;
 }
 
 bool caller_captures(hipStream_t st) {
@@ -902,13 +903,13 @@ bool caller_captures(hipStream_t st) {
   return false;
 }
 
-int plan_enqueue(fdtd_plan* p, int64_t n, hipStream_t st, Fork* fk, bool captured = false) {
+int plan_enqueue(fdtd_plan* p, int64_t n, hipStream_t st, Fork* fk) {
   int nt[FD_NCLASS];
   for (int c = 0; c < FD_NCLASS; ++c) nt[c] = (int)p->own.tiles[c].size();
   for (int64_t s = 0; s < n; ++s) {
     const int r = enqueue_step(p->own.dev, nt, p->own.part, p->own.pgrid, p->own.nflux, p->beyond, p->tune.tile_x, p->tune.block,
                                p->tune.max_blocks, p->ddft, (int)p->dft.size(), p->maxnf,
-                               plan_dft_due(p, p->step + s, captured), (int)s, p->ntst, plan_dm(p), st, fk);
+                               plan_dft_due(p, p->step + s), (int)s, p->ntst, plan_dm(p), st, fk);
     if (r) return r;
   }
   HIPCHK(fd_launch_advance_one(p->ddesc, n, st));
@@ -1568,6 +1569,7 @@ int fdtd_bind_arena(fdtd_plan* p, void* dev, size_t bytes, int64_t max_steps, vo
   if (int r = build_dm_units(p)) return r;
   HIPCHK(hipStreamSynchronize(st));
   p->step = 0;
+  p->captured = false;
   p->beyond = beyond_cache(p);
   p->ntst = p->tune.stores == FDTD_STORES_NONTEMPORAL ? 1
             : p->tune.stores == FDTD_STORES_ORDINARY ? 0
@@ -1592,8 +1594,10 @@ int fdtd_get_material_map(fdtd_plan* p, uint8_t* host_map, void* stream) {
 static int plan_step(fdtd_plan* p, int64_t n, hipStream_t st) {
   if (n < 0) return fail(FDTD_EINVAL, "negative step count");
   if (p->step + n > p->max_steps) return fail(FDTD_ESTATE, "max_steps (%lld) exceeded", (long long)p->max_steps);
-  if (n > 0 && caller_captures(st)) {
-    if (int r = plan_enqueue(p, n, st, nullptr, true)) return r;
+  const bool cap = n > 0 && caller_captures(st);
+  p->captured |= cap;
+  if (cap || (n > 0 && p->captured && !p->dft.empty())) {
+    if (int r = plan_enqueue(p, n, st, nullptr)) return r;
     p->step += n;
     return FDTD_OK;
   }
@@ -1907,7 +1911,7 @@ int fdtd_time_kernels(fdtd_plan* p, int64_t n, void* stream, double* ms, int64_t
       });
       if (r) { cleanup(); return r; }
     }
-    if (next_flush(p, p->step + s) == p->step + s) {
+    if (plan_dft_due(p, p->step + s)) {
       const int r = record(FD_KERNEL_DFT, [&](hipEvent_t a, hipEvent_t b) {
         return fd_launch_dft(p->ddft, (int)p->dft.size(), (int)s, st, a, b);
       });
@@ -2282,9 +2286,9 @@ void fdtd_batch_destroy(fdtd_batch* b) {
   delete b;
 }
 
-static bool group_dft_due(const fdtd_batch* b, const BGroup& g, int64_t s, bool captured) {
+static bool group_dft_due(const fdtd_batch* b, const BGroup& g, int64_t s) {
   for (int m = g.m0; m < g.m1; ++m)
-    if (plan_dft_due(b->plans[m], b->plans[m]->step + s, captured)) return true;
+    if (plan_dft_due(b->plans[m], b->plans[m]->step + s)) return true;
   return false;
 }
 
@@ -2300,14 +2304,14 @@ static DmLaunch group_dm(const fdtd_batch* b, const BGroup& g) {
 // n steps of every member, group after group (a group's state stays in the
 // Infinity Cache over its n steps when it fits there); members are independent,
 // so the order changes no result.
-static int batch_enqueue(fdtd_batch* b, int64_t n, hipStream_t st, Fork* fk, bool captured = false) {
+static int batch_enqueue(fdtd_batch* b, int64_t n, hipStream_t st, Fork* fk) {
   for (const BGroup& g : b->groups) {
     fd_tile* dt[FD_NCLASS];
     for (int c = 0; c < FD_NCLASS; ++c) dt[c] = b->dtiles[c] + g.t0[c];
     const DmLaunch dm = group_dm(b, g);
     for (int64_t s = 0; s < n; ++s) {
       const int r = enqueue_step(dt, g.nt, g.part, g.pgrid, g.nflux, g.beyond, b->tile_x, b->block, b->max_blocks, b->ddft + g.d0, g.nd,
-                                 g.maxnf, group_dft_due(b, g, s, captured), (int)s, b->ntst, dm, st, fk);
+                                 g.maxnf, group_dft_due(b, g, s), (int)s, b->ntst, dm, st, fk);
       if (r) return r;
     }
   }
@@ -2321,8 +2325,14 @@ static int batch_step(fdtd_batch* b, int64_t n, hipStream_t st) {
   for (fdtd_plan* p : b->plans)
     if (p->step + n > p->max_steps) return fail(FDTD_ESTATE, "a member would exceed its max_steps");
   // as plan_step; a run ends with the first DFT launch of any member
-  if (n > 0 && caller_captures(st)) {
-    if (int r = batch_enqueue(b, n, st, nullptr, true)) return r;
+  const bool cap = n > 0 && caller_captures(st);
+  bool eager = cap;
+  for (fdtd_plan* p : b->plans) {
+    p->captured |= cap;
+    eager |= p->captured && !p->dft.empty();
+  }
+  if (n > 0 && eager) {
+    if (int r = batch_enqueue(b, n, st, nullptr)) return r;
     for (fdtd_plan* p : b->plans) p->step += n;
     return FDTD_OK;
   }
@@ -2389,7 +2399,7 @@ int fdtd_batch_time_kernels(fdtd_batch* b, int64_t n, void* stream, double* ms, 
                                           b->ntst, g.nflux[c], step_rev(g.beyond, g.nu[0] > 0, s), st, a, z);
       if (e != hipSuccess) { cleanup(); return fail(FDTD_EHIP, "batch_time_kernels: %s", hipGetErrorString(e)); }
     }
-    if (group_dft_due(b, g, s, false) && g.nd > 0) {
+    if (group_dft_due(b, g, s) && g.nd > 0) {
       hipEvent_t a, z;
       if (int r = pair(FD_KERNEL_DFT, &a, &z)) { cleanup(); return r; }
       const hipError_t e = fd_launch_dft(b->ddft + g.d0, g.nd, (int)s, st, a, z);
