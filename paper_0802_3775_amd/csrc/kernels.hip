@@ -280,25 +280,28 @@ __global__ __launch_bounds__(256) void spectrum_kernel(const double* __restrict_
 // For reads: the partial sums of each T(t) or energy sample (a row of m) added in
 // order, as a host loop would, so that only one number per sample leaves the
 // device.  A workgroup stages kRowCols columns of kRows rows at a time in LDS
-// (coalesced loads), then a thread per row adds them up.
-constexpr int kRows = 16, kRowCols = 128;
+// (coalesced loads), then a thread per row adds them up.  At most kRowGroups
+// workgroups go over the rows in turn: they fill the chip, and a group for each of
+// the 2^31 samples that a plan may have would exceed a launch's 2^32 threads.
+constexpr int kRows = 16, kRowCols = 128, kRowGroups = 4096;
 __global__ __launch_bounds__(256) void row_sums_kernel(const double* __restrict__ part, long long n, int m,
                                                        double* __restrict__ out) {
   __shared__ double buf[kRows][kRowCols + 1];
-  const long long r0 = (long long)blockIdx.x * kRows;
-  double acc = 0.0;
-  for (int c0 = 0; c0 < m; c0 += kRowCols) {
-    const int w = min(kRowCols, m - c0);
-    for (int t = (int)threadIdx.x; t < kRows * kRowCols; t += 256) {
-      const int r = t / kRowCols, c = t % kRowCols;
-      if (r0 + r < n && c < w) buf[r][c] = part[(size_t)(r0 + r) * m + c0 + c];
+  for (long long r0 = (long long)blockIdx.x * kRows; r0 < n; r0 += (long long)gridDim.x * kRows) {
+    double acc = 0.0;
+    for (int c0 = 0; c0 < m; c0 += kRowCols) {
+      const int w = min(kRowCols, m - c0);
+      for (int t = (int)threadIdx.x; t < kRows * kRowCols; t += 256) {
+        const int r = t / kRowCols, c = t % kRowCols;
+        if (r0 + r < n && c < w) buf[r][c] = part[(size_t)(r0 + r) * m + c0 + c];
+      }
+      __syncthreads();
+      if (threadIdx.x < kRows && r0 + threadIdx.x < n)
+        for (int c = 0; c < w; ++c) acc += buf[threadIdx.x][c];
+      __syncthreads();
     }
-    __syncthreads();
-    if (threadIdx.x < kRows && r0 + threadIdx.x < n)
-      for (int c = 0; c < w; ++c) acc += buf[threadIdx.x][c];
-    __syncthreads();
+    if (threadIdx.x < kRows && r0 + threadIdx.x < n) out[r0 + threadIdx.x] = acc;
   }
-  if (threadIdx.x < kRows && r0 + threadIdx.x < n) out[r0 + threadIdx.x] = acc;
 }
 
 __global__ void advance_kernel(fd_desc* const* descs, int n, long long k) {
@@ -860,7 +863,8 @@ hipError_t fd_launch_spectrum(const double* acc, int nf, int plane, double* part
 
 hipError_t fd_launch_row_sums(const double* part, long long n, int m, double* out, hipStream_t st) {
   if (n <= 0 || m <= 0) return hipSuccess;
-  row_sums_kernel<<<(unsigned)((n + kRows - 1) / kRows), 256, 0, st>>>(part, n, m, out);
+  const long long groups = (n + kRows - 1) / kRows;
+  row_sums_kernel<<<(unsigned)(groups < kRowGroups ? groups : kRowGroups), 256, 0, st>>>(part, n, m, out);
   return hipGetLastError();
 }
 
