@@ -462,8 +462,15 @@ size_t pitched(const fdtd_plan* p, size_t o) { return (o / (size_t)p->g.nx) * (s
 // array moves in contiguous pieces and the padding is put in or left out on the
 // host: a 2-D copy to pageable memory goes one row at a time, 6.9 us each (one
 // component of a 200^3 grid took 274 ms).  Unpadded rows are one plain copy;
-// padded ones go through a buffer that stays in the CPU's cache.  Both return
-// with the copy done.
+// padded ones go through a buffer that stays in the CPU's cache.  Memory that HIP
+// knows (pinned, managed) takes the 2-D copy, which the GPU does on its own: a read
+// of that component 0.58 ms, through the pieces 3.2.  All return with the copy done.
+bool known_to_hip(const void* host) {
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, host) == hipSuccess) return a.type != hipMemoryTypeUnregistered;
+  (void)hipGetLastError();
+  return false;
+}
 constexpr size_t kRowPieceBytes = (size_t)2 << 20;
 template <class Piece>
 hipError_t row_pieces(const fdtd_plan* p, size_t elem, Piece&& piece) {
@@ -484,6 +491,11 @@ hipError_t copy_rows_to_device(const fdtd_plan* p, void* dev, const void* host, 
     return e == hipSuccess ? hipStreamSynchronize(st) : e;
   };
   if (p->px == p->g.nx) return copy(dev, host, w * (size_t)p->g.ny * p->g.nz);
+  if (known_to_hip(host)) {
+    const hipError_t e = hipMemcpy2DAsync(dev, elem * (size_t)p->px, host, w, w, (size_t)p->g.ny * p->g.nz,
+                                          hipMemcpyHostToDevice, st);
+    return e == hipSuccess ? hipStreamSynchronize(st) : e;
+  }
   return row_pieces(p, elem, [&](uint8_t* buf, size_t r0, size_t n, size_t pitch) {
     for (size_t r = 0; r < n; ++r) {
       std::memcpy(buf + r * pitch, (const uint8_t*)host + (r0 + r) * w, w);
@@ -499,6 +511,11 @@ hipError_t copy_rows_to_host(const fdtd_plan* p, void* host, const void* dev, si
     return e == hipSuccess ? hipStreamSynchronize(st) : e;
   };
   if (p->px == p->g.nx) return copy(host, dev, w * (size_t)p->g.ny * p->g.nz);
+  if (known_to_hip(host)) {
+    const hipError_t e = hipMemcpy2DAsync(host, w, dev, elem * (size_t)p->px, w, (size_t)p->g.ny * p->g.nz,
+                                          hipMemcpyDeviceToHost, st);
+    return e == hipSuccess ? hipStreamSynchronize(st) : e;
+  }
   return row_pieces(p, elem, [&](uint8_t* buf, size_t r0, size_t n, size_t pitch) {
     const hipError_t e = copy(buf, (const uint8_t*)dev + r0 * pitch, n * pitch);
     if (e != hipSuccess) return e;
