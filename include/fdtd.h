@@ -168,8 +168,8 @@ typedef struct {
    plan's most general kernel (one launch per step).  parallel: 1 makes the
    launches of a step parallel branches of the captured graph, 0 keeps them in
    stream order.  stores: FDTD_STORES_AUTO (non-temporal field stores for a plan
-   whose step state exceeds the 256 MiB Infinity Cache, ordinary ones otherwise
-   and in batches), FDTD_STORES_ORDINARY or FDTD_STORES_NONTEMPORAL.
+   whose step state exceeds the 256 MiB Infinity Cache and whose tiles write whole
+   cache lines, ordinary ones otherwise and in batches), FDTD_STORES_ORDINARY or FDTD_STORES_NONTEMPORAL.
    cache_mb (batches only; >= 0): members are stepped in groups of consecutive
    members whose step state together is at most cache_mb MB, each group for all
    the steps of a call (or of a captured graph) before the next, so that a group

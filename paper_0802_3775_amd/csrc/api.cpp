@@ -559,19 +559,31 @@ size_t step_state_bytes(const fdtd_plan* p) {
 }
 
 // Whether the state of a step (the gain arrays by the cells that have them) exceeds
-// the Infinity Cache.  Field stores then go out non-temporal: the next step finds
-// little of it there, and ordinary stores only displace what is still to be read.
-// Microseconds per step, ordinary against non-temporal, by state: Lorentz boxes
-// 195 MiB 89.3 / 99.6, 241 MiB 108.0 / 108.7, 485 MiB 156.6 / 150.5;
-// density-matrix boxes 229 MiB 158.7 / 162.6, 286 MiB 193.9 / 190.1, 457 MiB
-// 324.5 / 315.6; z-CPML slabs 255 MiB 78.6 / 73.6, 331 MiB 85.9 / 82.9; the
-// 200^3 box with CPML on all faces (440 MiB) 153.7 / 141.9.
+// the Infinity Cache.
 bool beyond_cache(const fdtd_plan* p) {
   size_t b = (size_t)p->ncell * 49;
   for (int w = 0; w < 3; ++w) b += 6 * 4 * psi_elems(p, w, true);
   if (p->gm == 1) b += (size_t)p->ncell * 4 + (size_t)p->hdesc.ngain * 48;
   if (p->gm == 2) b += (size_t)p->hdesc.ngain * 96;
   return b > kInfinityCacheBytes;
+}
+
+// Field stores of such a plan go out non-temporal if its tiles write whole 128-byte
+// lines: the next step finds little of the output in the cache, and ordinary stores
+// only displace what is still to be read.  Microseconds per step, ordinary against
+// non-temporal, by state: Lorentz boxes 195 MiB 89.3 / 99.6, 241 MiB 108.0 / 108.7,
+// 485 MiB 156.6 / 150.5; density-matrix boxes 229 MiB 158.7 / 162.6, 286 MiB
+// 193.9 / 190.1, 457 MiB 324.5 / 315.6; z-CPML slabs 255 MiB 78.6 / 73.6, 331 MiB
+// 85.9 / 82.9; the 200^3 box with CPML on all faces (440 MiB) 153.7 / 141.9.
+// A line written in part goes to HBM in part and is not merged with its rest: tiles
+// 16 wide (200^3 periodic 135 / 147, 320x320x408 640 / 695), and rows that start
+// inside a line (100x250x300, 32 wide 113 / 145, 64 wide 100 / 111; 130x450x450
+// 391 / 562 and 364 / 449).  Lines are whole where rows are a multiple of 32 cells
+// and tiles at least 32 wide, and nearly so where one tile holds whole rows of a
+// multiple of 8 cells, which follow each other (40x800x800, 64 wide 301 / 293,
+// 24x800x800, 32 wide 166 / 161; but 33x400x500, 64 wide 91.4 / 97.7).
+bool whole_line_stores(const fdtd_plan* p) {
+  return p->tune.tile_x >= 32 && (p->px % 32 == 0 || (p->g.nx <= p->tune.tile_x && p->px % 8 == 0));
 }
 
 // z ranges of the tiles: split at the CPML slab interfaces, then into chunks.
@@ -1590,7 +1602,7 @@ int fdtd_bind_arena(fdtd_plan* p, void* dev, size_t bytes, int64_t max_steps, vo
   p->beyond = beyond_cache(p);
   p->ntst = p->tune.stores == FDTD_STORES_NONTEMPORAL ? 1
             : p->tune.stores == FDTD_STORES_ORDINARY ? 0
-            : (p->beyond ? 1 : 0);
+            : (p->beyond && whole_line_stores(p) ? 1 : 0);
   p->bound = true;
   return FDTD_OK;
 }
