@@ -42,6 +42,7 @@ struct Ctx {
   R32<float> Hout[3];
   // CPML (used by the kernels specialised with PML)
   int lo[3], hi[3], t[3], n[3];
+  int wx, xhi;  // x slabs' psi: row length, start of the high slab's
   const cfloat* prof[3];  // read-only for the kernel: scalar loads where uniform
   R32<float> psiE[3][2];
   R32<const float> psiHin[3][2];
@@ -61,6 +62,10 @@ __device__ __forceinline__ void make_ctx(Ctx& x, const cdesc* d, int par, bool p
   }
   x.n[0] = d->nx; x.n[1] = d->ny; x.n[2] = d->nz;
   if (!pml) return;
+  // equal x slabs: an array each; else rows of both
+  const bool apart = d->pml_lo[0] == d->pml_hi[0];
+  x.wx = apart ? d->pml_lo[0] : d->pml_t[0];
+  x.xhi = apart ? d->pml_lo[0] * x.ny * x.nz : d->pml_lo[0];
 #pragma unroll
   for (int w = 0; w < 3; ++w) {
     x.lo[w] = d->pml_lo[w]; x.hi[w] = d->pml_hi[w]; x.t[w] = d->pml_t[w];
@@ -87,17 +92,25 @@ __device__ __forceinline__ int slab(const Ctx& x, int w, int p) {
 }
 
 // psi array offset for axis w, slab index sp, at (i, j, k).  z slabs are whole
-// planes.  The rows of y slabs have the fields' pitch, and each x slab is an array of
-// its own: a tile's rows of one x slab follow each other, where rows that held both
+// planes.  The rows of y slabs have the fields' pitch, and x slabs of equal width are an
+// array each: a tile's rows of one x slab follow each other, where rows that held both
 // slabs left most 128-byte lines to two tiles at the grid's two ends (200x200x200
 // box 138.1 -> 135.5 us; while interior tiles took the all-axes march too, 139.9 and
 // 140.3).
 __device__ __forceinline__ int psi_off(const Ctx& x, int w, int sp, int i, int j, int k) {
   if (w == 2) return sp * x.plane + j * x.rx + i;
   if (w == 1) return (k * x.t[1] + sp) * x.rx + i;
-  const bool up = sp >= x.lo[0];
-  return (k * x.ny + j) * (up ? x.hi[0] : x.lo[0]) + (up ? x.lo[0] * x.ny * x.nz + sp - x.lo[0] : sp);
+  return (k * x.ny + j) * x.wx + (sp < x.lo[0] ? sp : sp - x.lo[0] + x.xhi);
 }
+// The same for the x slabs by xslab(), which finds the high slab's place once per
+// lane: a product and a sum per plane remain.  A choice of the row length and the
+// start in every plane cost tiles in x slabs that work from the cache 2-7% (94x94x94
+// box, 64 wide, 26.7 us, rows of both slabs 26.1, this 26.0).
+__device__ __forceinline__ int xslab(const Ctx& x, int i) {
+  const int sp = slab(x, 0, i);
+  return sp < x.lo[0] ? sp : sp - x.lo[0] + x.xhi;
+}
+__device__ __forceinline__ int xpsi_off(const Ctx& x, int sx, int j, int k) { return (k * x.ny + j) * x.wx + sx; }
 
 // CPML stretch of one difference d along axis w at index p (E position when
 // HSIDE = false, H position when HSIDE = true): returns d/kappa + psi with the
@@ -504,10 +517,10 @@ __device__ __forceinline__ void run_tile(const fd_tile& tl, int s_rel, Lds<TX>& 
   const bool uxs = AX && x.t[0] > 0 && (i0 - 1 < x.lo[0] || i0 + TX > x.nx - x.hi[0]);
   const bool uys = AX && x.t[1] > 0 && (j0 - 1 < x.lo[1] || j0 + TY > x.ny - x.hi[1]);
   if (AX) {
-    sxo = slab(x, 0, i);
+    sxo = xslab(x, i);
     syo = slab(x, 1, j);
     if (hact) {
-      sxh = slab(x, 0, hgi);
+      sxh = xslab(x, hgi);
       syh = slab(x, 1, hgj);
     }
     if (t < 6 * (TX + 1)) s.gx[t / (TX + 1)][t % (TX + 1)] = gxv;
@@ -536,10 +549,10 @@ __device__ __forceinline__ void run_tile(const fd_tile& tl, int s_rel, Lds<TX>& 
     float aH[6] = {}, aE[6] = {}, aHh[4] = {}, gzE[3] = {}, gzH[3] = {};
     uint32_t ox = 0, oy = 0, oz = 0, ohx = 0, ohy = 0, ohz = 0;
     if (AX) {
-      ox = (act && sxo >= 0) ? (uint32_t)psi_off(x, 0, sxo, i, j, k) : 0u;
+      ox = (act && sxo >= 0) ? (uint32_t)xpsi_off(x, sxo, j, k) : 0u;
       oy = (act && syo >= 0) ? (uint32_t)psi_off(x, 1, syo, i, j, k) : 0u;
       oz = (act && sz >= 0) ? (uint32_t)(sz * x.plane + c) : 0u;
-      ohx = (hact && sxh >= 0) ? (uint32_t)psi_off(x, 0, sxh, hgi, hgj, k) : 0u;
+      ohx = (hact && sxh >= 0) ? (uint32_t)xpsi_off(x, sxh, hgj, k) : 0u;
       ohy = (hact && syh >= 0) ? (uint32_t)psi_off(x, 1, syh, hgi, hgj, k) : 0u;
       ohz = (hact && sz >= 0) ? (uint32_t)(sz * x.plane + h_off) : 0u;
       // own H: Hx(y, z), Hy(z, x), Hz(x, y); own E in the same order.  The
