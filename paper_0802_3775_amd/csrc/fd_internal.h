@@ -168,6 +168,17 @@ enum {
 // classes, the DFT, then the four density-matrix passes.
 enum { FD_KERNEL_DFT = FD_NCLASS, FD_KERNEL_DM = FD_NCLASS + 1, FD_NKERNEL = FD_NCLASS + 5 };
 
+// Whether the DFT samples of nflux flux planes (4 floats per thread each) go to the
+// ends of four E staging arrays of the step tile, which a tile of fewer than
+// FD_MAXBLOCK threads leaves free.  Else the launch has LDS of its own for them.
+// More LDS per workgroup leaves workgroups of 64 threads (tiles 16 wide) fewer waves:
+// 80x80x136 slab with gain 27.7 us, with 4 KiB a plane 34.8, with 1 KiB 34.1.  Wider
+// tiles have 128 threads or more and lose nothing to it, and the choice costs 1% of a
+// short step (39x26x102 slab 7.16 -> 7.23).
+static __host__ __device__ inline bool fd_sample_spare(int tile_x, int block, int nflux) {
+  return tile_x == 16 && nflux * block <= (FD_MAXBLOCK - block) / tile_x * (tile_x + 2);
+}
+
 // Launchers (kernels.hip).
 // A launch's tile list split into 8 contiguous parts of about equal cost, one
 // per XCD (workgroup w runs on XCD w mod 8).  count[x] = 0 parts are allowed.

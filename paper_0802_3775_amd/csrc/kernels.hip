@@ -812,10 +812,10 @@ hipError_t fd_launch_step(int cls, const fd_tile* tiles, int ntiles, int tile_x,
                           hipEvent_t stop) {
   if (ntiles <= 0) return hipSuccess;
   if (nflux < 0 || nflux > FD_MAXFLUX) return hipErrorInvalidValue;
-  const unsigned lds = (unsigned)(nflux * 4 * FD_MAXBLOCK * (int)sizeof(float));
   if (block < 64 || block > FD_MAXBLOCK || (block & 63) != 0 || grid <= 0 || block % tile_x != 0 ||
       2 * (tile_x + 2) + 2 * (block / tile_x) > block)
     return hipErrorInvalidValue;
+  const unsigned lds = fd_sample_spare(tile_x, block, nflux) ? 0u : (unsigned)(nflux * 4 * FD_MAXBLOCK * (int)sizeof(float));
   fd_xcd pz{};
   int use = 0;
   if (part) {

@@ -216,8 +216,8 @@ __device__ __forceinline__ float pre_apply(const PreStretch& r, float d) {
 template <int TX>
 struct Lds {
   static constexpr int TYM = FD_MAXBLOCK / TX;
-  static constexpr int W = TX + 2;
-  float E[2][3][(TYM + 2) * (TX + 2)];  // E^n, planes k and k+1, over [i0-1, i0+TX] x [j0-1, j0+TY]
+  static constexpr int W = TX + 2, N = (TYM + 2) * W;
+  float E[2][3][N];  // E^n, planes k and k+1, over [i0-1, i0+TX] x [j0-1, j0+TY]
   float H[3][(TYM + 1) * (TX + 1)];     // H^{n+1/2} of plane k over [i0-1, i0+TX-1] x [j0-1, j0+TY-1]
   fd_mat mat[FD_MAXMAT];
   double red[FD_MAXBLOCK / 64];
@@ -244,7 +244,7 @@ __device__ __forceinline__ bool energy_due(const cdesc* d, long long n) {
 // the other tiles' march has none of that code (nor its uniform values).
 template <int TX, int PM, int GAIN, bool ZT, bool NT, bool SP>
 __device__ __forceinline__ void run_tile(const fd_tile& tl, int s_rel, Lds<TX>& s) {
-  extern __shared__ float smp[];  // 4 x FD_MAXBLOCK floats per flux plane of the launch's tile with the most
+  extern __shared__ float smp[];  // DFT samples that do not fit into s.E (fd_sample_spare)
   const cdesc* d = (const cdesc*)tl.d;
   constexpr int W = Lds<TX>::W;
   const int TY = (int)blockDim.x / TX;
@@ -534,6 +534,21 @@ __device__ __forceinline__ void run_tile(const fd_tile& tl, int s_rel, Lds<TX>& 
       s.gy[r][q % (Lds<TX>::TYM + 1)] = (jj >= 0 && jj < x.ny && slab(x, 1, jj) >= 0) ? x.prof[1][r * x.ny + jj] : 0.0f;
     }
   }
+
+  // Where thread `at` has the DFT sample of flux plane f, and the stride of its four
+  // values: at the ends of four E arrays, or in the launch's own LDS
+  auto sample_at = [&](int f, int at, int& stride) __attribute__((always_inline)) -> float* {
+    const int r = __builtin_popcount(fmask & ((1u << f) - 1u));
+    if constexpr (TX == 16) {
+      const int bd = (int)blockDim.x;
+      if (fd_sample_spare(TX, bd, __builtin_popcount(fmask))) {
+        stride = Lds<TX>::N;
+        return &s.E[0][0][0] + Lds<TX>::N - (r + 1) * bd + at;
+      }
+    }
+    stride = FD_MAXBLOCK;
+    return smp + r * 4 * FD_MAXBLOCK + at;
+  };
 
   auto plane_step = [&](auto cbc, const int k, Stage& S) __attribute__((always_inline)) {
     constexpr int cb = decltype(cbc)::value;
@@ -899,11 +914,12 @@ __device__ __forceinline__ void run_tile(const fd_tile& tl, int s_rel, Lds<TX>& 
         // march, so that the march's loads and stores are the same on every path
         int at = t;
         __asm__("" : "+v"(at));  // formed here: hoisted out of the march it would take a register per plane
-        float* sv = smp + __builtin_popcount(fmask & ((1u << f) - 1u)) * 4 * FD_MAXBLOCK + at;
+        int st;
+        float* sv = sample_at(f, at, st);
         sv[0] = eo[0];
-        sv[FD_MAXBLOCK] = eo[1];
-        sv[2 * FD_MAXBLOCK] = 0.5f * (hxm + hx);
-        sv[3 * FD_MAXBLOCK] = 0.5f * (hym + hy);
+        sv[st] = eo[1];
+        sv[2 * st] = 0.5f * (hxm + hx);
+        sv[3 * st] = 0.5f * (hym + hy);
       }
     }
     hxm = hx;
@@ -933,9 +949,10 @@ __device__ __forceinline__ void run_tile(const fd_tile& tl, int s_rel, Lds<TX>& 
     const uint32_t si = (uint32_t)(((uint64_t)(uint32_t)n * d->div_decim[f][0]) >> d->div_decim[f][1]);  // n / decim
     if (d->flux_nf[f] == 0 || si * (uint32_t)d->flux_decim[f] != (uint32_t)n || !act) continue;
     gf* ring = G(d->flux_ring[f]) + (size_t)(si % FD_DFT_RING) * 4 * (size_t)x.plane + c;
-    const float* sv = smp + __builtin_popcount(fmask & ((1u << f) - 1u)) * 4 * FD_MAXBLOCK + t;
+    int st;
+    const float* sv = sample_at(f, t, st);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) ring[(size_t)q * (size_t)x.plane] = sv[q * FD_MAXBLOCK];
+    for (int q = 0; q < 4; ++q) ring[(size_t)q * (size_t)x.plane] = sv[q * st];
   }
   if (edue) {
     const double tot = block_sum(eacc, s.red);
