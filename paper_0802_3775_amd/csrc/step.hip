@@ -486,19 +486,10 @@ __device__ __forceinline__ void run_tile(const fd_tile& tl, int s_rel, Lds<TX>& 
   load_h(k0, SA, true);
   load_e(k0 + 2, SB, k0 + 1 < k1);
   load_h(k0 + 1, SB, k0 + 1 < k1);
-  // next plane of the march that holds a flux plane: looked up here, while the loads
-  // above are in flight, and after each of them.  A look at flux_k in every plane was a
-  // load that the plane waited for, and a launch waits for its slowest tile (80x80x224
-  // slab 19.3 -> 18.1 us, 160x160x224, 64 x 48 planes, 78.1 -> 74.6)
-  auto flux_from = [&](int from) {
-    int best = 0x7fffffff;
-    for (unsigned mm = fmask; mm; mm &= mm - 1u) {  // uniform
-      const int fk = d->flux_k[__builtin_ctz(mm)];
-      best = fk >= from && fk < best ? fk : best;
-    }
-    return best;
-  };
-  int nextf = flux_from(k0);
+  // the next plane of the march that holds a flux plane.  A look at flux_k in every
+  // plane was a load that the plane waited for, and a launch waits for its slowest
+  // tile (80x80x224 slab 19.3 -> 18.1 us, 160x160x224, 64 x 48 planes, 78.1 -> 74.6)
+  int nextf = SP ? tl.fluxk : FD_NOFLUX;
   // H^{n+1/2} at (i, j, k0-1); E^n at (i, j, k0) is already in LDS buffer 0
   float hxm = 0.0f, hym = 0.0f;
   if (AX) {
@@ -911,10 +902,13 @@ __device__ __forceinline__ void run_tile(const fd_tile& tl, int s_rel, Lds<TX>& 
     load_h(k + 2, S, k + 2 < k1);
     // transmitted power through flux planes at this k (uniform branch)
     if (SP && k == nextf) {
-      nextf = flux_from(k + 1);
+      nextf = FD_NOFLUX;
 #pragma unroll 1
       for (int f = 0; f < FD_MAXFLUX; ++f) {
-        if (!((fmask >> f) & 1u) || d->flux_k[f] != k) continue;
+        if (!((fmask >> f) & 1u)) continue;
+        const int fk = (fmask & (fmask - 1u)) ? d->flux_k[f] : k;
+        if (fk > k && fk < nextf) nextf = fk;
+        if (fk != k) continue;
         double v = 0.0;
         if (act) {
           const float sx = 0.5f * (eo[0] + ex_n), sy = 0.5f * (eo[1] + ey_n);
