@@ -296,8 +296,10 @@ __global__ __launch_bounds__(256) void row_sums_kernel(const double* __restrict_
         if (r0 + r < n && c < w) buf[r][c] = part[(size_t)(r0 + r) * m + c0 + c];
       }
       __syncthreads();
-      if (threadIdx.x < kRows && r0 + threadIdx.x < n)
-        for (int c = 0; c < w; ++c) acc += buf[threadIdx.x][c];
+      if (threadIdx.x < kRows && r0 + threadIdx.x < n) {
+#pragma unroll 16
+        for (int c = 0; c < w; ++c) acc += buf[threadIdx.x][c];  // LDS reads ahead of the sums
+      }
       __syncthreads();
     }
     if (threadIdx.x < kRows && r0 + threadIdx.x < n) out[r0 + threadIdx.x] = acc;
