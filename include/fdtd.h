@@ -160,9 +160,10 @@ typedef struct {
    the tile is tile_x x block/tile_x columns, and its one-cell halo ring,
    2 (tile_x + 2) + 2 block/tile_x cells, must not exceed block: 16 with any
    block, 32 with 128 or 256, 64 with 256); zchunk: z-planes per tile (>= 1; a
-   plan stepped alone takes shorter tiles where these would leave the GPU idle);
-   graph_steps: steps captured per hipGraph (0: no graph); max_blocks: upper
-   bound on resident workgroups for the tile loop (0: one per tile).
+   plan stepped alone with max_blocks 0 takes shorter tiles where these would leave
+   the GPU idle); graph_steps: steps captured per hipGraph (0: no graph); max_blocks:
+   upper bound on resident workgroups for the tile loop (0, or no fewer than tiles:
+   one per tile).
    merge: 0 one launch per tile class; 1 tiles without CPML run with the z-CPML
    kernel of the same gain flag (one launch for both); 2 every tile runs with the
    plan's most general kernel (one launch per step).  parallel: 1 makes the

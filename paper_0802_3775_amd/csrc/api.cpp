@@ -624,8 +624,10 @@ std::vector<std::pair<int, int>> z_chunks(const fdtd_plan* p, int zchunk) {
 // Microseconds per step by tiles (chunk): 16^3 cell 8 (4) 6.69, 32 (1) 4.32;
 // 32^3 cell 32 (4) 6.45, 128 (1) 4.19; 39x26x102 slab 208 (4) 8.39, 412 (2) 7.21,
 // 816 (1) 7.26; 64x64x120 slab 272 (8) 12.37, 448 (5) 10.40, 720 (3) 10.47,
-// 1,150 (2) 11.36; 80x80x224 slab 930 (8) 18.9, 1,500 (5) 20.5.  A bound on the
-// workgroups keeps the tuning's tiles.
+// 1,150 (2) 11.36; 80x80x224 slab 930 (8) 18.9, 1,500 (5) 20.5.  The rule knows no
+// grid's last wave (72^3 Lorentz box, 16 wide, 450 (4) 22.4, 650 (3) 24.8), so a bound
+// on the workgroups, even one that is not reached, keeps the tuning's tiles: the tuner
+// asks for the chunk it times.
 int own_zchunk(const fdtd_plan* p) {
   constexpr size_t kTilesAlone = 768;
   const int zc = std::max(1, p->tune.zchunk);
@@ -859,6 +861,9 @@ struct DmLaunch {
   int n[3] = {0, 0, 0};
 };
 
+// A bound that the launch's workgroups stay under changes nothing.
+bool looped(int max_blocks, int ntiles) { return max_blocks > 0 && max_blocks < ntiles; }
+
 int step_rev(bool beyond, bool dm, int64_t s) { return beyond && !dm ? (int)(s & 1) : 0; }
 
 int enqueue_step(fd_tile* const dtiles[FD_NCLASS], const int* ntiles, const fd_xcd* part,
@@ -875,8 +880,8 @@ int enqueue_step(fd_tile* const dtiles[FD_NCLASS], const int* ntiles, const fd_x
   for (int u = 0; u < nused; ++u) {
     const int c = used[u];
     const int nt = ntiles[c];
-    const int grid = max_blocks > 0 ? std::min(nt, max_blocks) : pgrid[c];
-    const fd_xcd* pc = max_blocks > 0 ? nullptr : &part[c];
+    const int grid = looped(max_blocks, nt) ? max_blocks : pgrid[c];
+    const fd_xcd* pc = looped(max_blocks, nt) ? nullptr : &part[c];
     hipStream_t on = st;
     if (par && u > 0) {
       on = fk->side[c];
@@ -1961,8 +1966,8 @@ int fdtd_time_kernels(fdtd_plan* p, int64_t n, void* stream, double* ms, int64_t
     for (int c = 0; c < FD_NCLASS; ++c) {
       const int nt = (int)p->own.tiles[c].size();
       if (nt == 0) continue;
-      const int grid = p->tune.max_blocks > 0 ? std::min(nt, p->tune.max_blocks) : p->own.pgrid[c];
-      const fd_xcd* pc = p->tune.max_blocks > 0 ? nullptr : &p->own.part[c];
+      const int grid = looped(p->tune.max_blocks, nt) ? p->tune.max_blocks : p->own.pgrid[c];
+      const fd_xcd* pc = looped(p->tune.max_blocks, nt) ? nullptr : &p->own.part[c];
       const int r = record(c, [&](hipEvent_t a, hipEvent_t b) {
         return fd_launch_step(c, p->own.dev[c], nt, p->tune.tile_x, p->tune.block, grid, (int)s, pc, p->ntst,
                               p->own.nflux[c], step_rev(p->beyond, !p->dmu[0].empty(), s), st, a,
@@ -2450,8 +2455,8 @@ int fdtd_batch_time_kernels(fdtd_batch* b, int64_t n, void* stream, double* ms, 
     for (int c = 0; c < FD_NCLASS; ++c) {
       const int nt = g.nt[c];
       if (nt == 0) continue;
-      const int grid = b->max_blocks > 0 ? std::min(nt, b->max_blocks) : g.pgrid[c];
-      const fd_xcd* pc = b->max_blocks > 0 ? nullptr : &g.part[c];
+      const int grid = looped(b->max_blocks, nt) ? b->max_blocks : g.pgrid[c];
+      const fd_xcd* pc = looped(b->max_blocks, nt) ? nullptr : &g.part[c];
       hipEvent_t a, z;
       if (int r = pair(c, &a, &z)) { cleanup(); return r; }
       const hipError_t e = fd_launch_step(c, b->dtiles[c] + g.t0[c], nt, b->tile_x, b->block, grid, (int)s, pc,

@@ -3,7 +3,8 @@
 A tuning is {tile_x, block, zchunk, graph_steps, max_blocks, merge, parallel}:
 the xy tile of a workgroup (tile_x x block/tile_x columns), the number of
 z-planes each tile marches, the number of steps captured in one hipGraph, an
-optional cap on resident workgroups, how tile classes are folded into launches
+optional cap on resident workgroups (the tuner's choices have one out of
+reach), how tile classes are folded into launches
 and whether a step's launches are parallel graph branches.  Fields are bit-identical for every tuning (each cell's
 arithmetic does not depend on the tiling), so the tuner is free to pick the
 fastest.  It times candidate tunings through the library's fdtd_tune (scratch plans of
@@ -15,7 +16,13 @@ import json
 import os
 import time
 
-CACHE_VERSION = 8
+CACHE_VERSION = 9
+
+# A bound on the workgroups that no launch reaches: with one, a plan stepped alone
+# runs the tiles it is given, where without a bound small plans shorten them.  So a
+# timing is that of the candidate's own zchunk, and a batch, which always runs the
+# given tiles, gets one that was timed.
+NO_BOUND = 1 << 30
 
 
 def _cache_path():
@@ -44,13 +51,15 @@ def candidates(cfg, quick=False):
     if quick:
         tiles = [(64, 256), (32, 256), (16, 256)]
     chunks = [8, 16, 48, 4, 32, 64, 2, 1]
+    if nx * ny * nz < 4_000_000:  # the chunks at which small grids fill the GPU differ by single planes
+        chunks += [6, 5, 3]
     out = []
     for (tx, b), z in itertools.product(tiles, chunks):
         if tx > 16 and tx > 2 * nx:
             continue
         if z > nz:
             continue
-        out.append({"tile_x": tx, "block": b, "zchunk": z, "max_blocks": 0, "merge": 1, "parallel": 0})
+        out.append({"tile_x": tx, "block": b, "zchunk": z, "max_blocks": NO_BOUND, "merge": 1, "parallel": 0})
     return out
 
 
