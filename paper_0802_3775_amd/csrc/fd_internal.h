@@ -124,11 +124,9 @@ struct fd_tile {
   int i0, j0, k0, k1;
   int tidx, blk;
   // sources, probes and flux planes that touch the tile (bit q = entry q)
-  unsigned srcmask : FD_MAXSRC, pmask : FD_MAXPROBE, fmask : FD_MAXFLUX;
-  int fluxk;  // the lowest of those flux planes (FD_NOFLUX: none)
+  unsigned srcmask, pmask, fmask;
   int flags;  // FD_TILE_ZSLAB: some plane of [k0, k1) lies in a z CPML slab
 };
-#define FD_NOFLUX 0x7fffffff
 #define FD_TILE_ZSLAB 1
 // A plan stepped alone in shorter tiles than its tuning's lists both: the tuning's
 // tiles run in the steps that record the energy (whose partial sums are per tile

@@ -442,10 +442,10 @@ __global__ void init_pop_kernel(const uint8_t* __restrict__ map, const float* __
 // own voxel.  Each pass reads what the previous one wrote for neighbouring
 // cells, so the passes are separate launches; a cell's rho is read and written
 // only by its own thread.
-// Memory bounds the passes: on the 168^3 box, 2.09 M gain cells, they count 266 MB in
-// 54 us, 499 MB in 105 us and 136 MB in 31 us, 4.4-4.9 TB/s beside the 5.1 TB/s of a
+// Memory bounds the passes: on the 168^3 box, 2.09 M gain cells, they count 271 MB in
+// 55 us, 508 MB in 106 us and 139 MB in 32 us, 4.4-4.9 TB/s beside the 5.1 TB/s of a
 // large copy.  Numbering the gain cells and edges in blocks of 8 x 8 rows with
-// neighbouring units on one XCD took the corrector's traffic from 636 MB to 499, and
+// neighbouring units on one XCD took the corrector's traffic from 636 MB to 508, and
 // neighbour offsets without wall tests and divisions its instructions from 1,200 to
 // 930 a wave and its registers from 135 to 112, four waves per SIMD instead of three:
 // 124 -> 112 us, the rest by the order of the passes (dm_unit).

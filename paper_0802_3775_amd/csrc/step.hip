@@ -17,10 +17,10 @@
 // z-1 from the read-only inputs instead of waiting for the owner: one pass over
 // HBM per step (E, H, material index in; E, H out).
 //
-// Work mapping.  A tile is `block` consecutive (i,j) columns of the flattened xy
-// plane (x fastest, so every wavefront reads 64 contiguous floats per array) and a
-// z range [k0, k1) that the workgroup marches upward, carrying the H^{n+1/2} of
-// plane k-1 in registers.  Tiles whose columns touch no CPML slab and no gain cell
+// Work mapping.  A tile is TX x block/TX (i,j) columns (x fastest: a wavefront reads
+// one run of 64 floats per array in tiles 64 wide, two of 32 or four of 16 in the
+// others) and a z range [k0, k1) that the workgroup marches upward, carrying the
+// H^{n+1/2} of plane k-1 in registers.  Tiles whose columns touch no CPML slab and no gain cell
 // run a specialised kernel without that code.
 #include "fd_device.h"
 
@@ -486,10 +486,24 @@ __device__ __forceinline__ void run_tile(const fd_tile& tl, int s_rel, Lds<TX>& 
   load_h(k0, SA, true);
   load_e(k0 + 2, SB, k0 + 1 < k1);
   load_h(k0 + 1, SB, k0 + 1 < k1);
-  // the next plane of the march that holds a flux plane.  A look at flux_k in every
-  // plane was a load that the plane waited for, and a launch waits for its slowest
-  // tile (80x80x224 slab 19.3 -> 18.1 us, 160x160x224, 64 x 48 planes, 78.1 -> 74.6)
-  int nextf = SP ? tl.fluxk : FD_NOFLUX;
+  // next plane of the march that holds a flux plane: looked up here, while the loads
+  // above are in flight, and after each of them.  A look at flux_k in every plane was a
+  // load that the plane waited for, and a launch waits for its slowest tile (80x80x224
+  // slab 19.3 -> 18.1 us, 160x160x224, 64 x 48 planes, 78.1 -> 74.6).  Not in the class
+  // without CPML, whose shortest steps pay for the registers (32^3 periodic cell 4.05,
+  // with it 4.16), nor with Lorentz gain, whose boxes have no flux planes (84^3, 32
+  // wide, 28.6 and 28.9); with the place in the tile's record that cell takes 4.03, but
+  // the 64x64x120 slab 9.85 instead of 9.76.
+  constexpr bool FNEXT = PM != 0 && GAIN == 0;
+  auto flux_from = [&](int from) {
+    int best = 0x7fffffff;
+    for (unsigned mm = fmask; mm; mm &= mm - 1u) {  // uniform
+      const int fk = d->flux_k[__builtin_ctz(mm)];
+      best = fk >= from && fk < best ? fk : best;
+    }
+    return best;
+  };
+  int nextf = FNEXT ? flux_from(k0) : 0;
   // H^{n+1/2} at (i, j, k0-1); E^n at (i, j, k0) is already in LDS buffer 0
   float hxm = 0.0f, hym = 0.0f;
   if (AX) {
@@ -901,14 +915,11 @@ __device__ __forceinline__ void run_tile(const fd_tile& tl, int s_rel, Lds<TX>& 
     // own inputs two planes ahead into the Stage just consumed
     load_h(k + 2, S, k + 2 < k1);
     // transmitted power through flux planes at this k (uniform branch)
-    if (SP && k == nextf) {
-      nextf = FD_NOFLUX;
+    if (FNEXT ? SP && k == nextf : fmask != 0u) {
+      if (FNEXT) nextf = flux_from(k + 1);
 #pragma unroll 1
       for (int f = 0; f < FD_MAXFLUX; ++f) {
-        if (!((fmask >> f) & 1u)) continue;
-        const int fk = (fmask & (fmask - 1u)) ? d->flux_k[f] : k;
-        if (fk > k && fk < nextf) nextf = fk;
-        if (fk != k) continue;
+        if (!((fmask >> f) & 1u) || d->flux_k[f] != k) continue;
         double v = 0.0;
         if (act) {
           const float sx = 0.5f * (eo[0] + ex_n), sy = 0.5f * (eo[1] + ey_n);
@@ -1003,7 +1014,9 @@ __device__ __forceinline__ void step_body(const fd_tile* __restrict__ tiles, int
   // tiles that have none; z-only CPML launches specialise their interior tiles, and
   // all-axes launches without gain their lean tiles off the x and y slabs, which lose
   // the psi registers and tests of those axes (a folded or merged launch holds them:
-  // 200x200x200 box 139.5 -> 138.0 us, with the x slabs apart 139.9 -> 135.4).
+  // 200x200x200 box 139.5 -> 138.0 us, with the x slabs apart 139.9 -> 135.4).  With gain
+  // they cost more than they save: a gain cell's state sets the registers of every
+  // march (168^3 Lorentz box 148.9 -> 151.8 us, 84^3, 32 wide, 29.3 -> 31.6).
   // Inlined by hand: as a call, which the compiler chose for the z-CPML class with
   // gain, the marches took 264 VGPRs instead of 146 (160x160x160, 111 us and 84).
   auto run = [&](const fd_tile& tl) __attribute__((always_inline)) {
