@@ -1002,7 +1002,7 @@ __device__ __forceinline__ int xcd_tile(int w, int n) {
 // FORM: 0 the partition, 1 the loop, 2 either.  The plain and all-axes classes with
 // Lorentz gain have the loop in kernels of their own: what it keeps in registers cost
 // the partition's form 17 VGPRs (32 wide: plain 142 -> 125 and four waves per SIMD,
-// all-axes 168 -> 154; 128x128x96 with gain 36.2 -> 33.4 us per step, the 168^3 box
+// all-axes 168 -> 151; 128x128x96 with gain 36.2 -> 33.4 us per step, the 168^3 box
 // 150.9 -> 148.6).  The z-CPML class with gain lost 1% apart (160^3 84.3 -> 85.1), the
 // classes without gain nothing or up to 0.7%; one call of the march for both forms
 // made every class slower (the 200^3 box 135.5 -> 149.3 us).
@@ -1064,7 +1064,7 @@ __device__ __forceinline__ void step_body(const fd_tile* __restrict__ tiles, int
   }
 }
 
-// All-axes CPML with Lorentz gain: held at three waves per SIMD (154 VGPRs; with 180,
+// All-axes CPML with Lorentz gain: held at three waves per SIMD (151 VGPRs; with 180,
 // two waves, the 168^3 box took 191 us per step instead of 150).
 template <int TX, int PM, int GAIN, bool NT>
 __global__ __launch_bounds__(FD_MAXBLOCK) __attribute__((amdgpu_waves_per_eu(PM == 7 && GAIN ? 3 : 1))) void step_kernel(
